@@ -161,8 +161,8 @@ oprag_status oprag_workspace_bytes(const oprag_index *idx, int32_t op, int64_t n
  *   q_dev      [nq x dim] in the index dtype;
  *   scores_dev [nq x k] fp32;  ids_dev [nq x k] int64 (row ids).
  * nq = 0 is a no-op.  workspace_dev must hold oprag_workspace_bytes(OPRAG_OP_DENSE) bytes.
- * Asynchronous on stream for every k (bf16 / fp16 searches with k > 16 run in threshold
- * levels whose exactness repair is decided on the device), so a search can be captured in a
+ * Asynchronous on stream for every k (searches that run in threshold levels decide their
+ * exactness repair on the device), so a search can be captured in a
  * HIP graph.
  */
 oprag_status oprag_search_dense(const oprag_index *idx, const void *q_dev, int64_t nq, int32_t k, float *scores_dev,
@@ -171,15 +171,14 @@ oprag_status oprag_search_dense(const oprag_index *idx, const void *q_dev, int64
 /*
  * For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): oprag_search_dense with the same
- * arguments, kernels and results, but no workspace argument.  The intermediate per-chunk
- * lists (or threshold-level candidates) go to a fixed array of OPRAG_NOALLOC_SCRATCH_BYTES
+ * arguments, kernels and results, but no workspace argument.  The intermediate results (group
+ * maxima, scores, threshold-level candidates) go to a fixed array of OPRAG_NOALLOC_SCRATCH_BYTES
  * in device memory that the library defines once per GPU and keeps until the process ends;
- * the call allocates nothing.  A search whose plan at the current row count needs more
- * returns E_CAPACITY with nothing enqueued: split the batch.  The need never exceeds what
- * oprag_workspace_bytes(OPRAG_OP_DENSE) reports; with k <= 16 and up to 1,024 queries it
- * stays within 8 MiB (2.6 MB for 256 queries and k = 5), while k > 16 needs 8 bytes per
- * query and candidate slot (every row up to 32,768 rows) and can exceed the array at a few
- * hundred queries.  Every call on one GPU shares its array, and nothing in it has to start
+ * the call allocates nothing.  A k <= 16 batch (fp32: any k) that needs more runs in equal parts
+ * that fit, one after another; a call returns E_CAPACITY with nothing enqueued (split the batch)
+ * if 8 bytes per query and result exceed the array, or, with k > 16 on a bf16 / fp16 index, the
+ * plan at the current row count does: that needs 8 bytes per query and candidate slot (every
+ * row up to 32,768 rows) and can exceed the array at a few hundred queries.  Every call on one GPU shares its array, and nothing in it has to start
  * at any value (each call writes what it later reads), so calls that may overlap on one GPU
  * (different streams, or several host threads) race and must be ordered by the caller.
  */
@@ -267,9 +266,9 @@ oprag_status oprag_search_hybrid_weighted(const oprag_index *idx, const void *q_
  * Kernel timing (diagnostics: measuring the scoring kernel against its roofline).  Arms a
  * pair of caller-created HIP events (hipEvent_t passed as void *) that the next dense
  * search issued from the calling thread records on its stream immediately before and after
- * its scoring kernel, the kernel that streams the index (the merge of per-chunk lists that
- * may follow stays outside the pair; with more than 2^20 queries only the first launch is
- * bracketed).  One-shot: the pair is disarmed once recorded.  NULL, NULL disarms.  The
+ * its scoring kernel, the kernel that streams the index (the selection that follows stays
+ * outside the pair; of a batch of more than 4,096 queries, which runs in equal parts, only the
+ * first is bracketed).  One-shot: the pair is disarmed once recorded.  NULL, NULL disarms.  The
  * library creates, keeps and destroys no event.
  */
 oprag_status oprag_time_next_dense_kernel(void *start_event, void *stop_event);

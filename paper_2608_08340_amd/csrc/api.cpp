@@ -98,7 +98,7 @@ oprag_status check_buf(const void* p, const char* name) {
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 size_t dense_ws(const oprag_index* idx, int64_t nq, int32_t k) {
-  const int nql = (int)std::min<int64_t>(nq, kMaxQPerLaunch);
+  const int nql = (int)std::min<int64_t>(nq, kMaxQPerLaunch);  // larger batches run in parts
   return oprag::dense_workspace_bound(idx->dtype, idx->dim, idx->capacity, nql, k, idx->n_cus);
 }
 
@@ -120,10 +120,10 @@ size_t dense_first_ws(const oprag_index* idx, int64_t nq, int32_t n_cand) {
 // Weighted fusion: dense scores, lexical scores (each [nq x ld], ld = capacity rounded up to
 // 4), composites [nq x capacity], counts [nq].
 long long weighted_ld(const oprag_index* idx) { return (idx->capacity + 3) & ~3ll; }
-// Partial minima and maxima per query: of the dense dump's chunks (at most as many as its plan
-// at full capacity has) and of the BM25 ranges.
+// Partial minima and maxima per query: of the dense dump's chunks (the most any row count gives)
+// and of the BM25 ranges.
 int weighted_pd(const oprag_index* idx, int64_t nq) {
-  return std::max(1, oprag::plan_dense_dump(idx->dtype, idx->dim, idx->capacity, (int)nq, idx->n_cus).n_chunks);
+  return oprag::dense_dump_chunks(idx->dtype, idx->dim, idx->capacity, (int)nq, idx->n_cus);
 }
 int weighted_pl(const oprag_index* idx) {
   return (int)((idx->capacity + oprag::kSparseRange - 1) / oprag::kSparseRange);
@@ -134,16 +134,16 @@ size_t weighted_ws(const oprag_index* idx, int64_t nq) {
          align_up((size_t)nq * (size_t)weighted_pd(idx, nq) * 8) + align_up((size_t)nq * (size_t)weighted_pl(idx) * 8);
 }
 
+// Runs the batch in equal parts of at most max_part queries, one after another on the stream.
 oprag_status do_dense(const oprag_index* idx, const void* q, int64_t nq, int32_t k, float* scores, int64_t* ids, void* ws,
-                      size_t ws_bytes, hipStream_t s) {
+                      size_t ws_bytes, hipStream_t s, int64_t max_part = kMaxQPerLaunch) {
   const size_t es = elem_size(idx->dtype);
-  for (int64_t q0 = 0; q0 < nq; q0 += kMaxQPerLaunch) {
-    const int nql = (int)std::min<int64_t>(kMaxQPerLaunch, nq - q0);
+  const int64_t parts = (nq + max_part - 1) / max_part, part = (nq + parts - 1) / parts;
+  for (int64_t q0 = 0; q0 < nq; q0 += part) {
+    const int nql = (int)std::min<int64_t>(part, nq - q0);
     const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, nql, k, idx->n_cus);
-    if (p.kernel < 0) return fail(OPRAG_E_UNSUPPORTED, "no dense kernel for dtype %d, k %d", idx->dtype, k);
-    if (oprag::dense_workspace_bytes(p, nql) > ws_bytes)
-      return fail(OPRAG_E_INVALID, "workspace too small: %zu < %zu bytes", ws_bytes,
-                  oprag::dense_workspace_bytes(p, nql));
+    const size_t need = oprag::dense_workspace_bytes(p, idx->dtype, idx->dim, nql, idx->n_rows, k);
+    if (need > ws_bytes) return fail(OPRAG_E_INVALID, "workspace too small: %zu < %zu bytes", ws_bytes, need);
     oprag::DenseArgs a;
     a.X = idx->slab;
     a.n_rows = idx->n_rows;
@@ -151,9 +151,6 @@ oprag_status do_dense(const oprag_index* idx, const void* q, int64_t nq, int32_t
     a.Q = static_cast<const unsigned char*>(q) + (size_t)q0 * idx->dim * es;
     a.nq = nql;
     a.k = k;
-    a.n_qblocks = p.n_qblocks;
-    a.n_chunks = p.n_chunks;
-    a.rows_per_chunk = p.rows_per_chunk;
     a.partial = static_cast<unsigned long long*>(ws);
     a.out_scores = scores + q0 * k;
     a.out_ids = reinterpret_cast<long long*>(ids) + q0 * k;
@@ -169,12 +166,11 @@ oprag_status do_dense(const oprag_index* idx, const void* q, int64_t nq, int32_t
   return OPRAG_OK;
 }
 
-// Largest workspace one call of a dense search without allocation may need.  The plan of
-// one launch (at most kMaxQPerLaunch queries) at the current row count decides it.
+// Workspace of one launch of nq queries at the current row count.
 size_t dense_ws_now(const oprag_index* idx, int64_t nq, int32_t k) {
-  const int nql = (int)std::min<int64_t>(nq, kMaxQPerLaunch);
-  const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, nql, k, idx->n_cus);
-  return p.kernel < 0 ? 0 : oprag::dense_workspace_bytes(p, nql);
+  nq = std::min<int64_t>(nq, (int64_t)1 << 30);
+  const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, (int)nq, k, idx->n_cus);
+  return oprag::dense_workspace_bytes(p, idx->dtype, idx->dim, (int)nq, idx->n_rows, k);
 }
 
 // The workspace of oprag_search_dense_noalloc: a fixed device array, one copy per GPU the
@@ -517,16 +513,22 @@ oprag_status oprag_search_dense_noalloc(const oprag_index* idx, const void* q_de
   if (oprag_status st = check_buf(q_dev, "q_dev")) return st;
   if (oprag_status st = check_buf(scores_dev, "scores_dev")) return st;
   if (oprag_status st = check_buf(ids_dev, "ids_dev")) return st;
-  const size_t need = dense_ws_now(idx, nq, k);
+  // A bf16 / fp16 search with k > 16 keeps a candidate slot of 8 bytes per query and row (or, over
+  // long indexes, per slot) and is refused where the whole batch does not fit; any other search
+  // runs in as many parts as the array asks for.
+  int64_t part = std::min<int64_t>(nq, kMaxQPerLaunch);
+  const bool whole = k > 16 && idx->dtype != OPRAG_F32;
+  const size_t need = whole ? dense_ws_now(idx, nq, k) : (size_t)nq * k * 8;
   if (need > kNoallocScratchBytes)
     return fail(OPRAG_E_CAPACITY, "search needs %zu bytes of scratch, the fixed array holds %zu (fewer queries per call)",
                 need, kNoallocScratchBytes);
+  while (part > 1 && dense_ws_now(idx, part, k) > kNoallocScratchBytes) part = (part + 1) / 2;
   DeviceScope ds(idx->device);
   if (ds.error() != hipSuccess) return hip_fail(ds.error(), "select device");
   void* ws = nullptr;
   if (oprag_status st = scratch_of(idx->device, &ws)) return st;
   if (oprag_status st = do_dense(idx, q_dev, nq, k, scores_dev, ids_dev, ws, kNoallocScratchBytes,
-                                 static_cast<hipStream_t>(stream)))
+                                 static_cast<hipStream_t>(stream), part))
     return st;
   return ok();
 }
@@ -683,7 +685,6 @@ oprag_status oprag_search_hybrid_weighted(const oprag_index* idx, const void* q_
   if (!workspace_dev || !aligned16(workspace_dev) || workspace_bytes < need)
     return fail(OPRAG_E_INVALID, "workspace missing or too small (%zu < %zu bytes)", workspace_bytes, need);
   const oprag::DensePlan p = oprag::plan_dense_dump(idx->dtype, idx->dim, idx->n_rows, (int)nq, idx->n_cus);
-  if (p.kernel < 0) return fail(OPRAG_E_UNSUPPORTED, "no scoring kernel for dtype %d", idx->dtype);
   DeviceScope ds(idx->device);
   if (ds.error() != hipSuccess) return hip_fail(ds.error(), "select device");
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -712,7 +713,7 @@ oprag_status oprag_search_hybrid_weighted(const oprag_index* idx, const void* q_
   a.dump = D;
   a.dump_ld = ld;
   a.dump_mm = mm_d;
-  hipError_t e = oprag::launch_dense_dump(p, a, s);
+  hipError_t e = oprag::launch_dense_dump(p, idx->dtype, a, s);
   if (idx->n_rows <= oprag::kSparseRange && idx->sp.n_docs <= oprag::kSparseRange) {
     // one range: the BM25 kernel fuses its scores with the dense dump and selects the top k
     if (e == hipSuccess)

@@ -10,8 +10,11 @@
 namespace oprag {
 
 constexpr int kMaxK = 128;                 // largest k any list may ask for
-constexpr int kMaxQPerLaunch = 1 << 20;    // queries per dense launch (the host splits larger batches)
+constexpr int kMaxQPerLaunch = 4096;       // queries per dense launch (the host splits larger batches evenly)
 constexpr int kDtypeF32 = 0, kDtypeBF16 = 1, kDtypeF16 = 2;
+
+// Modes of the tiled scoring kernel.
+enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2 };
 
 struct DenseArgs {
   const void* X;                // slab rows [n_rows x d]
@@ -22,59 +25,101 @@ struct DenseArgs {
   int k;
   int n_qblocks;
   int n_chunks;
-  long long rows_per_chunk;     // multiple of the kernel's tile rows
-  unsigned long long* partial;  // [nq x n_chunks x k] per-chunk lists (when n_chunks > 1)
+  long long tiles;              // chunk c takes row tiles [c tiles / n_chunks, (c + 1) tiles / n_chunks)
+  unsigned long long* partial;  // workspace
   float* out_scores;            // [nq x k]
   long long* out_ids;           // [nq x k]
-  // Filtered mode (k > 16): every row scoring >= th[q * th_stride] (all rows when th is null)
-  // becomes a candidate key in cbuf[q][0 .. cap); ccnt[q] counts them (and may exceed cap).
+  // Filter: every row scoring >= th[q * th_stride] becomes a candidate key in cbuf[q][0 .. cap);
+  // ccnt[q] counts them (and may exceed cap).  check_mask: tiles between looks at the workgroup's
+  // queue of hits, less one (a power of two less one).
   const float* th = nullptr;
   int th_stride = 0;
   unsigned long long* cbuf = nullptr;
   int* ccnt = nullptr;
   long long cap = 0;
+  int check_mask = 0;
+  long long row_base = 0;       // id of row 0 of X
   // When set, the launch does nothing unless *gate != 0 (a device-side overflow flag).
   const int* gate = nullptr;
-  // Score dump (SEL 3): every score to dump[q * dump_ld + row]; with dump_mm set, also the
-  // minimum and maximum of each (query, chunk) to dump_mm[(q * n_chunks + chunk) * 2 + {0, 1}].
+  // Score dump: every score to dump[q * dump_ld + row]; with dump_mm set, also the minimum and
+  // maximum of each (query, chunk) to dump_mm[(q * n_chunks + chunk) * 2 + {0, 1}].
   float* dump = nullptr;
   long long dump_ld = 0;
   float* dump_mm = nullptr;
+  // Group maxima: the largest score of each group (a lane's rows of mx_gs consecutive 16-row subtiles)
+  // to mx[q * mx_ld + group], and of each lane over its chunk to cmx[q * cmx_ld + ..] (NaN: no row;
+  // either may be null).
+  float* mx = nullptr;
+  long long mx_ld = 0;
+  int mx_gs = 1;
+  float* cmx = nullptr;
+  long long cmx_ld = 0;
 };
 
+// Maxima of one launch: groups of gs subtiles (a power of two), per_tile of a row tile, count in all;
+// coarse ones in all (0: none are kept).  The groups' row stride ld, the coarse ones' cld.
+struct MaxGroups {
+  int gs = 1, per_tile = 0, count = 0, coarse = 0;
+  long long ld = 0, cld = 0;
+};
+
+// The k best rows from a launch's maxima (gate as above).  Lane l of a tile (wave row and lane
+// quarter, 1 << lanes_sh of them) has 1 << mt_sh subtiles in groups of 1 << gs_sh (1 << gl_sh of them);
+// group ((tile << lanes_sh) + l << gl_sh) + i, coarse maximum (chunk << lanes_sh) + l, and chunk
+// c has tiles [c tiles / n_chunks, (c + 1) tiles / n_chunks), at most `most`.
+struct RescoreArgs {
+  const void* X = nullptr;
+  const void* Q = nullptr;
+  long long n_rows = 0;
+  int d = 0, k = 0;
+  const float* fine = nullptr;   // null: the coarse maxima are the groups
+  int two = 0;                   // the groups are searched through the coarse maxima
+  long long fine_ld = 0;
+  int n_fine = 0;
+  const float* coarse = nullptr;
+  long long coarse_ld = 0;
+  int n_coarse = 0;
+  int tile_rows = 0, n_chunks = 1, most = 0;
+  int least = 0, spare = 0;      // tiles / n_chunks, tiles % n_chunks
+  int gpt_sh = 0, lanes_sh = 0, gl_sh = 0, gs_sh = 0, mt_sh = 0;
+  float* out_scores = nullptr;
+  long long* out_ids = nullptr;
+  const int* gate = nullptr;
+};
+
+// Launchers of one storage type (dense_tile_*.hip).
+template <int DT>
+hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipStream_t s, hipEvent_t ev0,
+                       hipEvent_t ev1);
+template <int DT>
+hipError_t rescore_launch(const RescoreArgs& a, int nq, hipStream_t s);
+
+// How a search of one launch runs (dense.hip): group maxima and rescoring, every score and a
+// selection, or threshold levels.
 struct DensePlan {
+  enum Kind { kMaxima, kDump, kFilter };
+  Kind kind = kMaxima;
   int n_cus = 0;                // compute units of the device the plan is for
-  int kernel = 0;               // index into the dense kernel table
-  int bn = 0;                   // queries per workgroup
-  int tile_rows = 0;            // rows per tile
-  int n_qblocks = 0;
-  int n_chunks = 0;
-  long long rows_per_chunk = 0;
-  long long cap = 0;            // partial-list slots per query (bounds n_chunks * k)
-  long long grid = 0;
-  size_t lds_bytes = 0;
-  // Filtered mode: candidate passes over growing row prefixes, each one's k-th score the next
-  // one's threshold; the last level is all rows.
-  bool filtered = false;
+  int shape = 0;                // tile shape over all rows
+  long long ld = 0;             // kDump: row stride of the scores
+  MaxGroups groups;             // kMaxima, and kFilter's first level
+  // kFilter
+  int shape0 = 0;               // tile shape of the first level
   int n_levels = 0;
-  long long level_rows[8] = {};
-  long long fcap = 0;           // candidate slots per query
-  bool repair = false;          // a level can overflow fcap: enqueue the device-gated repair
-  long long chunk_bound = 0;    // workgroups per query block the filter passes aim for
-  // The first level's kernel: a small-tile one when the main kernel would leave most CUs idle
-  // on the first level's few rows.
-  int kernel0 = 0;
-  int n_qblocks0 = 0;
-  long long chunk_bound0 = 0;
+  long long level_rows[16] = {};
+  long long cap = 0;            // candidate slots per query
+  MaxGroups groups_all;         // exact fallback: coarse maxima over all rows,
+  int cus_all = 0;              // in as many chunks as this many CUs would get
+  int n_chunks = 0;             // plan_dense_dump: chunks of the launch
 };
 
 DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cus);
-// The per-chunk-list plan for any k (the exact fallback of the filtered mode).
-DensePlan plan_dense_lists(int dtype, int d, long long n_rows, int nq, int k, int n_cus);
-size_t dense_workspace_bytes(const DensePlan& p, int nq);
-// Score dump: every score of nq queries against rows [0, a.n_rows) into a.dump (SEL 3 kernel).
+size_t dense_workspace_bytes(const DensePlan& p, int dtype, int d, int nq, long long n_rows, int k);
+// Score dump: every score of nq queries against rows [0, a.n_rows) into a.dump.
 DensePlan plan_dense_dump(int dtype, int d, long long n_rows, int nq, int n_cus);
-hipError_t launch_dense_dump(const DensePlan& p, const DenseArgs& a, hipStream_t s);
+// The most chunks such a plan has at any row count up to `capacity`.
+int dense_dump_chunks(int dtype, int d, long long capacity, int nq, int n_cus);
+hipError_t launch_dense_dump(const DensePlan& p, int dtype, const DenseArgs& a, hipStream_t s);
 // Weighted fusion of dense scores D and lexical scores B ([nq x ld], lexical 0 past n_lex),
 // min-max normalised per query over n chunks, then the exact top k (cbuf [nq x n], ccnt [nq]).
 // The minima and maxima come from the dumps' partials mm_d [nq x pd x 2] and mm_l [nq x pl x 2].
@@ -83,11 +128,11 @@ hipError_t launch_weighted_fuse(int n_cus, const float* D, const float* B, long 
                                 unsigned long long* cbuf, int* ccnt, float* out_scores, long long* out_ids,
                                 hipStream_t s);
 // Plans take the compute-unit count of the index's device (the grid aims at a multiple of it).
-// Enough workspace for a search of nq queries at any row count up to `capacity`.
+// Enough workspace for a search of up to nq queries at any row count up to `capacity`.
 size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k, int n_cus);
-// ev0 / ev1 (optional) are recorded on s right before and after the scoring kernel (in
-// filtered mode, the last level's).  Filtered mode also enqueues its exactness repair:
-// launches gated on device-side overflow flags, so the search never waits for the host.
+// ev0 / ev1 (optional) are recorded on s right before and after the scoring kernel (threshold
+// levels: the last level's).  Threshold levels also enqueue their exactness repair: launches
+// gated on device-side overflow flags, so the search never waits for the host.
 hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipStream_t s, hipEvent_t ev0 = nullptr,
                         hipEvent_t ev1 = nullptr);
 

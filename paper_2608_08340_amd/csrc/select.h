@@ -37,26 +37,6 @@ __device__ __forceinline__ uint32_t comp_key(u64 c) { return (uint32_t)(c >> 32)
 __device__ __forceinline__ u64 umax64(u64 a, u64 b) { return a > b ? a : b; }
 __device__ __forceinline__ u64 umin64(u64 a, u64 b) { return a < b ? a : b; }
 
-// Per-thread sorted (descending) list of the KS best composites seen so far.
-template <int KS>
-struct RegTopK {
-  u64 v[KS];
-  __device__ __forceinline__ void clear() {
-#pragma unroll
-    for (int i = 0; i < KS; ++i) v[i] = 0ull;
-  }
-  // Top-KS of v + {x}: new[i] = max(v[i], min(v[i-1], x)), new[0] = max(v[0], x).
-  __device__ __forceinline__ void insert(u64 x) {
-#pragma unroll
-    for (int i = KS - 1; i > 0; --i) v[i] = umax64(v[i], umin64(v[i - 1], x));
-    v[0] = umax64(v[0], x);
-  }
-  // Lowest score that could still enter the list (-inf while it is not full).
-  __device__ __forceinline__ float floor_score() const {
-    return v[KS - 1] ? comp_score(v[KS - 1]) : -__builtin_inff();
-  }
-};
-
 // ------------------------------------------------------------------ wave64 bitonic network
 
 __device__ __forceinline__ u64 shfl_xor64(u64 x, int m) {
