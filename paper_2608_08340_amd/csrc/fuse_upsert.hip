@@ -98,13 +98,19 @@ __global__ void convert8_kernel(const float4* __restrict__ src, uint4* __restric
 // Embedding tail fused with the upsert (Section 4.3: mean pool over the chunk's tokens, then L2
 // normalisation; Section 3.2: Op_upsert).  One workgroup of 1,024 threads per chunk.  Thread t
 // owns eight consecutive dimensions 8 (t % 128) + 1024 b of every block b and the tokens
-// congruent to p = t / 128 modulo 8: it sums them in fp32 (16-byte loads of eight dimensions,
-// four tokens in flight), the eight partial sums are added through LDS in the order p = 0 .. 7,
-// and the squares of the sums are added in fp64.  The chunk's vector is sum / ||sum|| (the mean's 1/len cancels), rounded to
-// the slab dtype, or 0 when len = 0 or the sum is 0.  len is clamped to [0, T].
+// congruent to p = t / 128 modulo 8: it sums them in fp32 (16-byte loads, eight of them in flight),
+// the eight partial sums are added through LDS in the order p = 0 .. 7, and the squares of the sums
+// are added in fp64.  The chunk's vector is sum / ||sum|| (the mean's 1/len cancels), rounded to the
+// slab dtype, or 0 when len = 0 or the sum is 0.  len is clamped to [0, T].
+//
+// Bound by the longest chunk: one CU reads it, and its rate is the bytes it has in flight over the
+// latency.  256 chunks of up to 512 tokens of 1,024 bf16: 42 us with eight loads a thread in flight (the
+// last ones predicated, where single tokens used to be waited for one by one), 51 with four; twelve
+// gained nothing more, and two sets of eight in turn spill.
 constexpr int kPoolThreads = 1024;
 constexpr int kPoolLanes = 128;                         // threads per token residue
 constexpr int kPoolPar = kPoolThreads / kPoolLanes;     // token residues (8)
+constexpr int kPoolDeep = 8;                            // 16-byte loads of a thread in flight
 template <int HT>
 __device__ __forceinline__ void load8(const void* p, long long idx, int valid, float (&v)[8]) {
   if constexpr (HT == kDtypeF32) {
@@ -137,6 +143,9 @@ template <int HT, int DT>
 __global__ __launch_bounds__(kPoolThreads) void pool_upsert_kernel(const void* __restrict__ hidden,
                                                                    const int* __restrict__ lengths, int T, int h,
                                                                    void* __restrict__ rows) {
+  constexpr int kEs = HT == kDtypeF32 ? 4 : 2;  // element size
+  constexpr int kPer = kEs / 2;                 // 16-byte loads of eight dimensions
+  constexpr int kTok = kPoolDeep / kPer;        // tokens of a set
   __shared__ float sums[kMaxPoolDim];
   __shared__ float part[kPoolPar - 1][kPoolLanes * 8];
   __shared__ double red[kPoolThreads / 64];
@@ -151,22 +160,51 @@ __global__ __launch_bounds__(kPoolThreads) void pool_upsert_kernel(const void* _
     const int d0 = blk * 8 * kPoolLanes + 8 * c;
     const int valid = d0 >= h ? 0 : (vec ? 8 : min(8, h - d0));
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int tok = valid > 0 ? par : len;  // a thread past the last dimension sums nothing
-    for (; tok + 3 * kPoolPar < len; tok += 4 * kPoolPar) {  // four tokens, kPoolPar apart
-      float v[4][8];
+    if (vec) {
+      const int end = valid > 0 ? len : 0;  // a thread past the last dimension sums nothing
+      const uint4* src = reinterpret_cast<const uint4*>(static_cast<const unsigned char*>(hidden) +
+                                                        ((i * T) * (long long)h + d0) * kEs);
+      const long long step = (long long)h * kEs / 16;  // 16-byte words per token
+      for (int tok = par; tok < end; tok += kPoolPar * kTok) {
+        uint4 x[kPoolDeep];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        load8<HT>(hidden, ((i * T) + tok + kPoolPar * u) * (long long)h + d0, valid, v[u]);
+        for (int u = 0; u < kTok; ++u) {
+          const int tk = tok + kPoolPar * u;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+          for (int p = 0; p < kPer; ++p) x[u * kPer + p] = tk < end ? src[tk * step + p] : uint4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s[e] += v[u][e];
-    }
-    for (; tok < len; tok += kPoolPar) {
-      float v[8];
-      load8<HT>(hidden, ((i * T) + tok) * (long long)h + d0, valid, v);
+        for (int u = 0; u < kPoolDeep; ++u) {  // (+0 past the last token)
+          const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s[e] += v[e];
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (HT == kDtypeF32) {
+              s[(u % kPer) * 4 + e] += __uint_as_float(w[e]);
+            } else {
+              s[2 * e] += __uint_as_float(w[e] << 16);  // bf16 -> fp32 is exact
+              s[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
+            }
+          }
+        }
+      }
+    } else {
+      int tok = valid > 0 ? par : len;
+      for (; tok + 3 * kPoolPar < len; tok += 4 * kPoolPar) {  // four tokens, kPoolPar apart
+        float v[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          load8<HT>(hidden, ((i * T) + tok + kPoolPar * u) * (long long)h + d0, valid, v[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[e] += v[u][e];
+      }
+      for (; tok < len; tok += kPoolPar) {
+        float v[8];
+        load8<HT>(hidden, ((i * T) + tok) * (long long)h + d0, valid, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += v[e];
+      }
     }
     if (par > 0) {
 #pragma unroll
