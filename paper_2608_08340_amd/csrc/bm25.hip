@@ -19,10 +19,14 @@
 // postings in the range to an fp32 accumulator in LDS (128 KiB), one term after another with a
 // barrier in between, the next term's postings loading while the current one is added; a
 // term's postings name distinct chunks, so there are no atomics and the result is
-// deterministic.  The range's top-k then comes from a threshold (the k-th largest of the 256
+// deterministic.  The range's top-k then comes from a threshold (the k-th largest of the 64 or 256
 // maxima of groups of four threads) and exact ranks of the few scores at or above it, with the
 // keys held in registers; many scores above the threshold, or few positive ones, fall back to a
 // 4 x 8-bit radix select and a wave-wide bitonic sort (score desc, chunk asc).
+//
+// Of 26 us for a query of the 32,768-chunk corpus (the hybrid's, k = 50 to 100) the head rows take 9 (their
+// bytes at the CU's load rate), the terms' parse 2.4 (dependent reads), the tail terms 3 and the
+// selection 5: sixteen waves on four SIMDs, so instructions per key count there.
 #include <algorithm>
 
 #include "oprag_internal.h"
@@ -97,19 +101,18 @@ __global__ void prepare_kernel(int vocab, long long n_docs, long long nnz, const
   }
 }
 
-// Block-wide exclusive prefix sum of one int per thread (kNT threads).
+// Exclusive prefix sum of one int per thread of a block of N threads.  Every step is short: wave
+// sums by moves within the rows of 16 lanes, and the totals of all waves read at once (shuffles and
+// a loop over the waves before this one took 0.4 us more in a block of 1,024).
+template <int N>
 __device__ __forceinline__ int block_excl_scan(int v, int* wave_tot) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  const int x = wave_incl_scan(v);
   if (lane == 63) wave_tot[w] = x;
   __syncthreads();
   int before = 0;
-  for (int i = 0; i < w; ++i) before += wave_tot[i];
+#pragma unroll
+  for (int i = 0; i < N / 64; ++i) before += i < w ? wave_tot[i] : 0;
   __syncthreads();
   return before + x - v;
 }
@@ -246,39 +249,42 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
     int row = -1;
     float wt = 0.f;
     long long tlo = 0, thi = 0;
-    float twt = 0.f;
-    if (j < te) {
-      const int t = a.qterms[j];
-      if (t >= 0 && t < a.vocab) {
-        const int h = a.hidx[t];
-        if (h >= 0 || (early && j < tb + kTermBatch)) {
-          bool earlier = false;
-          int mult = 0;
-          for (int jj = tb; jj < te; ++jj)
-            if (a.qterms[jj] == t) {
-              if (jj < j) earlier = true;
-              else ++mult;
-            }
-          if (!earlier) {
-            if (h >= 0) {
-              row = h;
-              wt = a.idfk[t] * (float)mult;
-            } else {
-              tlo = a.indptr[t];
-              thi = a.indptr[t + 1];
-              twt = a.idfk[t] * (float)mult;
-            }
-          }
-        }
+    const int t = j < te ? a.qterms[j] : -1;
+    if (t >= 0 && t < a.vocab) {  // everything about the term is asked for at once, a repeat's too
+      row = a.hidx[t];
+      wt = a.idfk[t];
+      if (early && j < tb + kTermBatch) {
+        tlo = a.indptr[t];
+        thi = a.indptr[t + 1];
       }
     }
+    bool earlier = false;
+    int mult = 0;
+    if (te - tb <= 64) {  // workgroup-uniform: every term is in a lane of the first wave
+      if (w == 0)
+        for (int jj = 0; jj < te - tb; ++jj) {
+          const bool same = __builtin_amdgcn_readlane(t, jj) == t;
+          earlier |= same && jj < tid;
+          mult += same && jj >= tid ? 1 : 0;
+        }
+    } else if (row >= 0 || tlo < thi) {
+      for (int jj = tb; jj < te; ++jj)
+        if (a.qterms[jj] == t) {
+          if (jj < j) earlier = true;
+          else ++mult;
+        }
+    }
+    wt *= (float)mult;
+    if (earlier || row >= 0) tlo = thi = 0;
+    if (earlier) row = -1;
+    const float twt = wt;
     if (early && j0 == tb && tid < kTermBatch) {
       s_lo[tid] = tlo;
       s_hi[tid] = thi;
       s_wt[tid] = twt;
     }
     const int f = row >= 0 ? 1 : 0;
-    const int pos = nh + block_excl_scan(f, wave_tot);
+    const int pos = nh + block_excl_scan<kBT>(f, wave_tot);
     if (f) {  // distinct head terms <= kMaxHead
       hl_row[pos] = row;
       hl_wt[pos] = wt;
@@ -476,6 +482,13 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
     // maximum from the dump's partials.  Keys become score_key(fused), nonzero for every
     // chunk below wn (all are candidates), 0 past it; they replace the scores in LDS for the
     // selection below.
+    const float* drow = a.wdense + (long long)q * a.wld;
+    f32x4 x[8];  // on their way while the minima and maxima are found
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      const int c0 = 4 * tid + kLayer * g;  // 16-byte aligned: wld is a multiple of 4
+      x[g] = c0 < a.wn ? *reinterpret_cast<const f32x4*>(drow + c0) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     float mnd = __builtin_inff(), mxd = -__builtin_inff(), mnl = __builtin_inff(), mxl = -__builtin_inff();
     for (int i = tid; i < a.wpd; i += kBT) {
       mnd = fminf(mnd, a.wmm[((long long)q * a.wpd + i) * 2]);
@@ -487,12 +500,10 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
         mnl = fminf(mnl, __uint_as_float(kv[j]));
         mxl = fmaxf(mxl, __uint_as_float(kv[j]));
       }
-    for (int o = 32; o > 0; o >>= 1) {
-      mnd = fminf(mnd, __shfl_xor(mnd, o));
-      mxd = fmaxf(mxd, __shfl_xor(mxd, o));
-      mnl = fminf(mnl, __shfl_xor(mnl, o));
-      mxl = fmaxf(mxl, __shfl_xor(mxl, o));
-    }
+    mnd = wave_min(mnd);
+    mxd = wave_max(mxd);
+    mnl = wave_min(mnl);
+    mxl = wave_max(mxl);
     float* red = reinterpret_cast<float*>(cand);  // [4][kBT / 64]; the candidate area is free
     if (lane == 0) {
       red[w] = mnd;
@@ -510,15 +521,13 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
     }
     const double sd = mxd > mnd ? a.wd / ((double)mxd - (double)mnd) : 0.0;
     const double sl = mxl > mnl ? a.wl / ((double)mxl - (double)mnl) : 0.0;
-    const float* drow = a.wdense + (long long)q * a.wld;
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
-      const int c0 = 4 * tid + kLayer * g;  // 16-byte aligned: wld is a multiple of 4
-      const f32x4 x = c0 < a.wn ? *reinterpret_cast<const f32x4*>(drow + c0) : f32x4{0.f, 0.f, 0.f, 0.f};
+      const int c0 = 4 * tid + kLayer * g;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = 4 * g + e;
-        kv[j] = c0 + e < a.wn ? score_key(fused_value(sd, sl, mnd, mnl, x[e], __uint_as_float(kv[j]))) : 0u;
+        kv[j] = c0 + e < a.wn ? score_key(fused_value(sd, sl, mnd, mnl, x[g][e], __uint_as_float(kv[j]))) : 0u;
       }
       reinterpret_cast<uint4*>(acc)[tid + kBT * g] = make_uint4(kv[4 * g], kv[4 * g + 1], kv[4 * g + 2], kv[4 * g + 3]);
     }
@@ -539,39 +548,56 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
   };
   // chunks that hold keys: the range's, or in weighted mode every chunk below wn
   const int slen = weighted ? (int)a.wn : len;
-  // Threshold: the 256 groups of four adjacent threads (128 chunks each) take their largest
-  // key, and tau = the k-th largest of these maxima.  Every maximum is the key of its own
-  // chunk, so at least k chunks score >= tau and the top k lie among them.  Each of a group's
-  // threads counts the maxima above and equal to its group's in a quarter of the list.
+  // Threshold: groups of adjacent threads take their largest key, and tau = the k-th largest of
+  // these maxima.  Every maximum is the key of its own chunk, so at least k chunks score >= tau and
+  // the top k lie among them.  k <= 16: 64 groups of 16 threads (512 chunks each), each thread
+  // counting the maxima above its group's among four of them; otherwise 256 groups of four, each
+  // thread counting in a quarter of the list, which is 16 times the comparisons (2.0 us
+  // against 0.7, and 2.8 with those equal counted as well).
   {
     uint32_t m = 0u;
 #pragma unroll
     for (int j = 0; j < 32; ++j) m = max(m, kv[j]);
-    m = max(m, (uint32_t)__shfl_xor((int)m, 1));
-    m = max(m, (uint32_t)__shfl_xor((int)m, 2));
-    const int grp = tid >> 2, sub = tid & 3;
-    // four blocks of 64 maxima, 68 words apart, so the blocks the four threads read start in
-    // different LDS banks
+    m = max(m, (uint32_t)dpp<0xB1>((int)m));
+    m = max(m, (uint32_t)dpp<0x4E>((int)m));
     uint32_t* gmax = reinterpret_cast<uint32_t*>(cand);
-    if (sub == 0) gmax[(grp >> 6) * 68 + (grp & 63)] = m;
     if (tid == 0) {
-      s_tau = 0u;
+      s_tau = ~0u;
       s_nc = 0;
     }
-    __syncthreads();
-    int gt = 0, eq = 0;
-    const uint4* blk = reinterpret_cast<const uint4*>(gmax + sub * 68);
+    int gt = 0;  // maxima above the group's
+    bool first;  // of the group's threads
+    if (a.k <= 16) {  // launch-uniform
+      m = max(m, (uint32_t)dpp<0x141>((int)m));
+      m = max(m, (uint32_t)dpp<0x140>((int)m));
+      const int sub = tid & 15;
+      first = sub == 0;
+      if (first) gmax[tid >> 4] = m;
+      __syncthreads();
+      const uint4 x = reinterpret_cast<const uint4*>(gmax)[sub];
+      gt = (x.x > m ? 1 : 0) + (x.y > m ? 1 : 0) + (x.z > m ? 1 : 0) + (x.w > m ? 1 : 0);
+      gt += dpp<0xB1>(gt);
+      gt += dpp<0x4E>(gt);
+      gt += dpp<0x141>(gt);
+      gt += dpp<0x140>(gt);
+    } else {
+      const int grp = tid >> 2, sub = tid & 3;
+      first = sub == 0;
+      // four blocks of 64 maxima, 68 words apart, so the blocks the four threads read start in
+      // different LDS banks
+      if (first) gmax[(grp >> 6) * 68 + (grp & 63)] = m;
+      __syncthreads();
+      const uint4* blk = reinterpret_cast<const uint4*>(gmax + sub * 68);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const uint4 x = blk[u];
-      gt += (x.x > m ? 1 : 0) + (x.y > m ? 1 : 0) + (x.z > m ? 1 : 0) + (x.w > m ? 1 : 0);
-      eq += (x.x == m ? 1 : 0) + (x.y == m ? 1 : 0) + (x.z == m ? 1 : 0) + (x.w == m ? 1 : 0);
+      for (int u = 0; u < 16; ++u) {
+        const uint4 x = blk[u];
+        gt += (x.x > m ? 1 : 0) + (x.y > m ? 1 : 0) + (x.z > m ? 1 : 0) + (x.w > m ? 1 : 0);
+      }
+      gt += dpp<0xB1>(gt);
+      gt += dpp<0x4E>(gt);
     }
-    gt += __shfl_xor(gt, 1);
-    gt += __shfl_xor(gt, 2);
-    eq += __shfl_xor(eq, 1);
-    eq += __shfl_xor(eq, 2);
-    if (sub == 0 && m != 0u && gt <= a.k - 1 && a.k - 1 < gt + eq) s_tau = m;  // the k-th largest maximum
+    // the k-th largest maximum is the least with fewer than k above it
+    if (first && gt < a.k) atomicMin(&s_tau, m);
     __syncthreads();
   }
   const uint32_t tau = s_tau;  // 0: fewer than k positive maxima
@@ -594,15 +620,18 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
     // Otherwise the G above tau are ranked and, when G < k, ranks G .. k - 1 go to the chunks
     // equal to tau in chunk order (many chunks can share a score exactly: equal term
     // frequencies and lengths).  G + E >= k always.
-    uint32_t mgt = 0u, meq = 0u;
+    // (Two instructions a key; what equals tau is told apart only among the few that reach it.)
+    uint32_t mge = 0u, mgt = 0u;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      mgt |= (kv[j] > tau ? 1u : 0u) << j;
-      meq |= (kv[j] == tau ? 1u : 0u) << j;
+    for (int j = 31; j >= 0; --j) mge = mge + mge + (kv[j] >= tau ? 1u : 0u);
+    for (uint32_t msk = mge; msk != 0u; msk &= msk - 1u) {
+      const int j = __builtin_ctz(msk);
+      mgt |= (keys[own(j)] > tau ? 1u : 0u) << j;
     }
+    const uint32_t meq = mge & ~mgt;
     // both counts in one scan: G and E are at most 32,768, so the low field never carries
     const int packed = __popc(mgt) | (__popc(meq) << 16);
-    const int before = block_excl_scan(packed, wave_tot);
+    const int before = block_excl_scan<kBT>(packed, wave_tot);
     if (tid == kBT - 1) s_nc = before + packed;
     __syncthreads();
     const int G = s_nc & 0xffff, E = s_nc >> 16;
@@ -642,7 +671,7 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
           const int o = (i + tid) % nb;
           mk |= (keys[b0 + o] == tau ? 1u : 0u) << o;
         }
-        int rr = G + block_excl_scan(__popc(mk), wave_tot);
+        int rr = G + block_excl_scan<kBT>(__popc(mk), wave_tot);
         for (uint32_t m2 = mk; m2 != 0u && rr < a.k; m2 &= m2 - 1u) emit(rr++, composite(b0 + __builtin_ctz(m2)));
       }
       if (rrf) rrf_tail();
@@ -719,7 +748,7 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
       ++n_eq;
     }
   }
-  const int before = block_excl_scan(n_eq, wave_tot);
+  const int before = block_excl_scan<kBT>(n_eq, wave_tot);
   if (!take_all && n_eq && before < (int)need_eq) {
     const unsigned int ngt = (unsigned int)a.k - need_eq;
     int r = before;

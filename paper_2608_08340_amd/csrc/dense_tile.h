@@ -620,24 +620,6 @@ constexpr int kReCand = 64;                              // groups ranked by a w
 constexpr int kReList = 256;                             // groups scored: k + the groups of one tile
 constexpr int kReRows = 1024;                            // rows ranked together
 
-// A lane's value moved in its row of 16 (a tenth of a shuffle's latency): 0xB1, 0x4E lane ^ 1, ^ 2;
-// 0x141, 0x140 mirrored in 8, in 16; 0x110 + n from lane - n; 0x142, 0x143 the last lane of a row to
-// the next row, of two rows to the next two.  A lane without a source keeps its own.
-template <int CTRL>
-__device__ __forceinline__ int dpp(int x) {
-  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
-}
-__device__ __forceinline__ float wave_max(float x) {
-  auto step = [&](float y) { x = __builtin_fmaxf(x, y); };
-  step(__int_as_float(dpp<0x111>(__float_as_int(x))));
-  step(__int_as_float(dpp<0x112>(__float_as_int(x))));
-  step(__int_as_float(dpp<0x114>(__float_as_int(x))));
-  step(__int_as_float(dpp<0x118>(__float_as_int(x))));
-  step(__int_as_float(dpp<0x142>(__float_as_int(x))));
-  step(__int_as_float(dpp<0x143>(__float_as_int(x))));
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-
 template <int DT>
 __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
   if (a.gate != nullptr && *a.gate == 0) return;

@@ -37,6 +37,37 @@ __device__ __forceinline__ uint32_t comp_key(u64 c) { return (uint32_t)(c >> 32)
 __device__ __forceinline__ u64 umax64(u64 a, u64 b) { return a > b ? a : b; }
 __device__ __forceinline__ u64 umin64(u64 a, u64 b) { return a < b ? a : b; }
 
+// ------------------------------------------------------------------ lanes of a wave
+
+// A lane's value moved in its row of 16 (a tenth of a shuffle's latency): 0xB1, 0x4E lane ^ 1, ^ 2;
+// 0x141, 0x140 mirrored in 8, in 16; 0x110 + n from lane - n; 0x142, 0x143 the last lane of a row to
+// the next row, of two rows to the next two.  A lane without a source keeps its own.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
+}
+__device__ __forceinline__ float wave_max(float x) {
+  auto step = [&](float y) { x = __builtin_fmaxf(x, y); };
+  step(__int_as_float(dpp<0x111>(__float_as_int(x))));
+  step(__int_as_float(dpp<0x112>(__float_as_int(x))));
+  step(__int_as_float(dpp<0x114>(__float_as_int(x))));
+  step(__int_as_float(dpp<0x118>(__float_as_int(x))));
+  step(__int_as_float(dpp<0x142>(__float_as_int(x))));
+  step(__int_as_float(dpp<0x143>(__float_as_int(x))));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ float wave_min(float x) { return -wave_max(-x); }
+// Sum over the lanes up to this one.
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // rows 2 and 3
+  return x;
+}
+
 // ------------------------------------------------------------------ wave64 bitonic network
 
 __device__ __forceinline__ u64 shfl_xor64(u64 x, int m) {
