@@ -19,8 +19,8 @@
 // postings in the range to an fp32 accumulator in LDS (128 KiB), one term after another with a
 // barrier in between, the next term's postings loading while the current one is added; a
 // term's postings name distinct chunks, so there are no atomics and the result is
-// deterministic.  The range's top-k then comes from a threshold (the k-th largest of the 64 or 256
-// maxima of groups of four threads) and exact ranks of the few scores at or above it, with the
+// deterministic.  The range's top-k then comes from a threshold (the k-th largest of the
+// maxima of 64 or 256 groups of threads) and exact ranks of the few scores at or above it, with the
 // keys held in registers; many scores above the threshold, or few positive ones, fall back to a
 // 4 x 8-bit radix select and a wave-wide bitonic sort (score desc, chunk asc).
 //
@@ -1038,9 +1038,8 @@ __global__ __launch_bounds__(kDfThreads) void dense_first_kernel(int vocab, long
     }
     for (int i = t; i < kDfCand * kTerms; i += kDfThreads) wq[i / kTerms][i % kTerms] = 0.f;
     __syncthreads();
-    // sixteen entries per thread and step, all loads issued before any comparison; per query
-    // term the weights of matching entries are summed (a list holds a term once, so the sum
-    // is that weight or 0) and a match is stored
+    // sixteen entries per thread and step, all loads issued before any comparison; a list holds a
+    // term once, so at most one entry matches, and a match is stored
     for (long long f = f0 + j; f < f1; f += kStep * kDfLanes) {
       if (!pre) load_step(f);
       pre = false;
@@ -1049,7 +1048,7 @@ __global__ __launch_bounds__(kDfThreads) void dense_first_kernel(int vocab, long
         if (tu < 0) continue;  // uniform: the term takes part at an earlier occurrence, or never
         float m = 0.f;
 #pragma unroll
-        for (int v = 0; v < kStep; ++v) m += tm[v] == tu ? wt[v] : 0.f;
+        for (int v = 0; v < kStep; ++v) m = tm[v] == tu ? wt[v] : m;
         if (m != 0.f) wq[c][u] = m;
       }
     }
@@ -1077,9 +1076,9 @@ __global__ __launch_bounds__(kDfThreads) void dense_first_kernel(int vocab, long
   // ranking: the eight threads of candidate c each compare it with 16 of the candidates
   // (u = 16 j .. 16 j + 15); the counts are summed across the eight adjacent lanes
   auto sum8 = [](int x) {
-    x += __shfl_xor(x, 1);
-    x += __shfl_xor(x, 2);
-    x += __shfl_xor(x, 4);
+    x += dpp<0xB1>(x);
+    x += dpp<0x4E>(x);
+    x += dpp<0x141>(x);
     return x;
   };
   constexpr int kPer = kDfCand / kDfLanes;

@@ -131,29 +131,31 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(const void* __restrict_
       float m = kNegInf;
 #pragma unroll
       for (int u = 0; u < 8; ++u) m = fmaxf(m, wm[u]);
-#pragma unroll
-      for (int o = 1; o < GS; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+      if constexpr (GS == 4) {
+        m = fmaxf(m, __int_as_float(dpp<0xB1>(__float_as_int(m))));
+        m = fmaxf(m, __int_as_float(dpp<0x4E>(__float_as_int(m))));
+      }
       // blocks of the maxima, four floats of padding apart, so that the threads of a group read
       // from different banks
       float* fm = reinterpret_cast<float*>(gmax);
+      if (t == 0) s_tau = ~0ull;
       if (sub == 0) fm[(grp / GB) * (GB + 4) + grp % GB] = m;
       __syncthreads();
-      int gt = 0, eq = 0;
+      int gt = 0;
       const float4* blk = reinterpret_cast<const float4*>(fm + sub * (GB + 4));
 #pragma unroll 4
       for (int u = 0; u < GB / 4; ++u) {
         const float4 x = blk[u];
         gt += (x.x > m ? 1 : 0) + (x.y > m ? 1 : 0) + (x.z > m ? 1 : 0) + (x.w > m ? 1 : 0);
-        eq += (x.x == m ? 1 : 0) + (x.y == m ? 1 : 0) + (x.z == m ? 1 : 0) + (x.w == m ? 1 : 0);
       }
-#pragma unroll
-      for (int o = 1; o < GS; o <<= 1) {
-        gt += __shfl_xor(gt, o);
-        eq += __shfl_xor(eq, o);
+      if constexpr (GS == 4) {
+        gt += dpp<0xB1>(gt);
+        gt += dpp<0x4E>(gt);
       }
-      if (sub == 0 && gt <= need - 1 && need - 1 < gt + eq) s_tau = (u64)__float_as_uint(m);
+      // the need-th largest maximum is the least with fewer than need above it
+      if (sub == 0 && gt < need) atomicMin(&s_tau, (u64)score_key(m));
       __syncthreads();
-      ftau = __uint_as_float((uint32_t)s_tau);  // one value: every group with it writes the same
+      ftau = key_score((uint32_t)s_tau);
     } else {
       u64 m = 0ull;
       if (in_reg) {
