@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
         OPRAG_ADV(xk, xt)
         vm_wait<2 * AI + 2 * BI>();
       } else {
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < LA; ++u) {
           OPRAG_LDA(0, xk, xt, u * BUF)
           OPRAG_LDB(0, xk, u * BUF)
@@ -314,37 +314,42 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
             // fourth tile, 355 now), so the maxima of 32 tiles are kept and leave together, the four
             // lanes of a query exchanging them for 16 bytes of one tile each.
             static_assert(NT == 1);
-            const int e = t & 3, tq = (t >> 2) & 7;
-            mq[0] = e == 0 ? m[0] : mq[0];
-            mq[1] = e == 1 ? m[0] : mq[1];
-            mq[2] = e == 2 ? m[0] : mq[2];
-            mq[3] = e == 3 ? m[0] : mq[3];
-            const bool end = t == n_tiles - 1;
-            if (a.mx != nullptr && (e == 3 || end)) {
+            if (n_tiles == 1) {  // workgroup-uniform: nothing to wait for later, and little code to fetch
+              if (a.mx != nullptr && q < a.nq)
+                a.mx[(long long)q * a.mx_ld + (tile0 / BM) * (S::WM * 4) + wm * 4 + (lane >> 4)] = m[0];
+            } else {
+              const int e = t & 3, tq = (t >> 2) & 7;
+              mq[0] = e == 0 ? m[0] : mq[0];
+              mq[1] = e == 1 ? m[0] : mq[1];
+              mq[2] = e == 2 ? m[0] : mq[2];
+              mq[3] = e == 3 ? m[0] : mq[3];
+              const bool end = t == n_tiles - 1;
+              if (a.mx != nullptr && (e == 3 || end)) {
 #pragma unroll
-              for (int u = 0; u < 8; ++u)
-                if (tq == u) mw[u] = mq;
-              if (end || (tq == 7 && e == 3)) {
-                const int h = lane >> 4;
-                float* dst = a.mx + (long long)q * a.mx_ld + (tile0 / BM - (t & 31)) * (S::WM * 4) + wm * 4;
+                for (int u = 0; u < 8; ++u)
+                  if (tq == u) mw[u] = mq;
+                if (end || (tq == 7 && e == 3)) {
+                  const int h = lane >> 4;
+                  float* dst = a.mx + (long long)q * a.mx_ld + (tile0 / BM - (t & 31)) * (S::WM * 4) + wm * 4;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                  if (4 * u > (t & 31)) break;
-                  float y[4];  // from lane h ^ o of the query, for tile 4 u + h
+                  for (int u = 0; u < 8; ++u) {
+                    if (4 * u > (t & 31)) break;
+                    float y[4];  // from lane h ^ o of the query, for tile 4 u + h
 #pragma unroll
-                  for (int o = 0; o < 4; ++o) {
-                    const int c = h ^ o;
-                    const float x = c & 2 ? (c & 1 ? mw[u][3] : mw[u][2]) : (c & 1 ? mw[u][1] : mw[u][0]);
-                    y[o] = o == 0 ? x : __shfl_xor(x, 16 * o);
+                    for (int o = 0; o < 4; ++o) {
+                      const int c = h ^ o;
+                      const float x = c & 2 ? (c & 1 ? mw[u][3] : mw[u][2]) : (c & 1 ? mw[u][1] : mw[u][0]);
+                      y[o] = o == 0 ? x : __shfl_xor(x, 16 * o);
+                    }
+                    f32x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                      const int c = h ^ r;
+                      v[r] = c & 2 ? (c & 1 ? y[3] : y[2]) : (c & 1 ? y[1] : y[0]);
+                    }
+                    if (q < a.nq && 4 * u + h <= (t & 31))
+                      *reinterpret_cast<f32x4*>(dst + (long long)(4 * u + h) * (S::WM * 4)) = v;
                   }
-                  f32x4 v;
-#pragma unroll
-                  for (int r = 0; r < 4; ++r) {
-                    const int c = h ^ r;
-                    v[r] = c & 2 ? (c & 1 ? y[3] : y[2]) : (c & 1 ? y[1] : y[0]);
-                  }
-                  if (q < a.nq && 4 * u + h <= (t & 31))
-                    *reinterpret_cast<f32x4*>(dst + (long long)(4 * u + h) * (S::WM * 4)) = v;
                 }
               }
             }
