@@ -101,18 +101,18 @@ __global__ void prepare_kernel(int vocab, long long n_docs, long long nnz, const
   }
 }
 
-// Exclusive prefix sum of one int per thread of a block of N threads.  Every step is short: wave
-// sums by moves within the rows of 16 lanes, and the totals of all waves read at once (shuffles and
-// a loop over the waves before this one took 0.4 us more in a block of 1,024).
+// Exclusive prefix sum of one number per thread of a block of N threads (modulo 2^32).  Every step is
+// short: wave sums by moves within the rows of 16 lanes, and the totals of all waves read at once
+// (shuffles and a loop over the waves before this one took 0.4 us more in a block of 1,024).
 template <int N>
-__device__ __forceinline__ int block_excl_scan(int v, int* wave_tot) {
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_tot) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int x = wave_incl_scan(v);
+  const uint32_t x = wave_incl_scan(v);
   if (lane == 63) wave_tot[w] = x;
   __syncthreads();
-  int before = 0;
+  uint32_t before = 0u;
 #pragma unroll
-  for (int i = 0; i < N / 64; ++i) before += i < w ? wave_tot[i] : 0;
+  for (int i = 0; i < N / 64; ++i) before += i < w ? wave_tot[i] : 0u;
   __syncthreads();
   return before + x - v;
 }
@@ -208,9 +208,9 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
   __shared__ __attribute__((aligned(16))) u64 cand[kCandCap];
   unsigned int* hist = reinterpret_cast<unsigned int*>(cand);  // [256]
   u64* selbuf = cand + 128;                                    // [kMaxK]
-  __shared__ int s_nc;
+  __shared__ uint32_t s_nc;
   __shared__ uint32_t s_tau;
-  __shared__ int wave_tot[kBT / 64];
+  __shared__ uint32_t wave_tot[kBT / 64];
   __shared__ unsigned int s_prefix, s_need, s_take_all, s_ngt;
   __shared__ long long s_lo[kTermBatch], s_hi[kTermBatch];
   __shared__ float s_wt[kTermBatch];
@@ -629,15 +629,17 @@ __global__ __launch_bounds__(kBT) void bm25_kernel(SparseArgs a) {
       mgt |= (keys[own(j)] > tau ? 1u : 0u) << j;
     }
     const uint32_t meq = mge & ~mgt;
-    // both counts in one scan: G and E are at most 32,768, so the low field never carries
-    const int packed = __popc(mgt) | (__popc(meq) << 16);
-    const int before = block_excl_scan<kBT>(packed, wave_tot);
+    // Both counts in one scan, G in the low half and E in the high one.  G + E is at most 32,768
+    // and E at least 1, so the low half never carries; E is 32,768 when a whole range ties, which
+    // takes the top bit: the arithmetic is unsigned.
+    const uint32_t packed = (uint32_t)__popc(mgt) | ((uint32_t)__popc(meq) << 16);
+    const uint32_t before = block_excl_scan<kBT>(packed, wave_tot);
     if (tid == kBT - 1) s_nc = before + packed;
     __syncthreads();
-    const int G = s_nc & 0xffff, E = s_nc >> 16;
+    const int G = (int)(s_nc & 0xffffu), E = (int)(s_nc >> 16);
     const bool all = G + E <= kCandCap;  // workgroup-uniform
     if (G <= kCandCap) {
-      int pos = all ? (before & 0xffff) + (before >> 16) : (before & 0xffff);
+      int pos = (int)(all ? (before & 0xffffu) + (before >> 16) : (before & 0xffffu));
       for (uint32_t msk = all ? (mgt | meq) : mgt; msk != 0u; msk &= msk - 1u)
         cand[pos++] = composite(own(__builtin_ctz(msk)));
       __syncthreads();

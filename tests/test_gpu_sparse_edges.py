@@ -44,3 +44,34 @@ def test_bm25_terms_and_threshold_edges(terms, k):
         # fp32 sums of up to 130 products of values rounded to fp32: (130 + 2) 2^-24 < 1e-5
         rep = accept.check_ranked(B[q], ids[q], sc[q], k, rtol=1e-5, ranked=B[q] > 0)
         assert rep.ok, (q, rep.problems)
+
+
+@pytest.mark.parametrize("n", [32767, 32768])
+@pytest.mark.parametrize("k", [5, 16, 17, 128])
+def test_a_whole_range_of_equal_scores(n, k):
+    """Every chunk of a full range (32,768) has the same score, so the count of ties fills its half of
+    the packed counts: identical chunks for BM25 and the hybrid, a zero (padding) query without
+    matching terms for the weighted search.  The k smallest ids win."""
+    dev = device()
+    vocab = 4
+    csr = synth.csr_from_tokens(np.arange(n + 1, dtype=np.int64) * 2, np.tile(np.array([1, 2], np.int32), n), vocab)
+    idx = make_index(torch.zeros((n, 128), dtype=torch.bfloat16), "bf16")
+
+    def t(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+
+    idx.attach_sparse(t(csr.term_indptr), t(csr.post_chunk), t(csr.post_tf), t(csr.doc_len), 1.2, 0.75)
+    q = torch.zeros((3, 128), dtype=torch.bfloat16, device=dev)
+    qi = t(np.array([0, 1, 2, 4], np.int32))
+    first = np.tile(np.arange(k), (3, 1))
+    log("whole range of ties", n, k)
+    sc, ids = idx.search_sparse(qi, t(np.array([1, 2, 1, 2], np.int32)), k)
+    assert np.array_equal(ids.cpu().numpy(), first)
+    assert (sc == sc[:, :1]).all() and (sc > 0).all()
+    fused, fids = idx.search_hybrid(q, qi, t(np.array([1, 2, 1, 2], np.int32)), k, k, 60, k)
+    assert np.array_equal(fids.cpu().numpy(), first)
+    for terms in ([1, 2, 1, 2], [0, 0, 0, 0]):  # constant lexical rows: every fused score is 0
+        sc, ids = idx.search_hybrid_weighted(q, qi, t(np.array(terms, np.int32)), 0.5, 0.5, k)
+        assert np.array_equal(ids.cpu().numpy(), first)
+        assert (sc == 0).all()
+    idx.close()
