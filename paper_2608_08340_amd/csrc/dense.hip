@@ -517,14 +517,15 @@ int log2i(long long x) {
   return l;
 }
 
-// Most row tiles of a chunk.
+// Most row tiles of a chunk: 32-bit byte offsets reach past it, and its row offsets fit the
+// kChunkRowBits bits that a queued hit has for them (fp32 rows of up to 12 dimensions are the ones
+// short enough for that to count).
 long long max_tiles(const ShapeInfo& sh, int dtype, int d) {
-  return std::max(1ll, (1ll << 30) / ((long long)sh.bm * d * elem_bytes(dtype)));
+  return std::max(1ll, std::min((1ll << 30) / ((long long)sh.bm * d * elem_bytes(dtype)), (1ll << kChunkRowBits) / sh.bm));
 }
 
 // Chunks of one launch: row tiles divided as evenly as they go over at most one workgroup per CU
-// (rounded down, so that the grid is one round), and few enough rows per chunk that 32-bit byte
-// offsets reach past them.
+// (rounded down, so that the grid is one round), and no more tiles per chunk than max_tiles.
 struct TileGrid {
   int n_qblocks = 1, n_chunks = 1;
   long long tiles = 0, most = 0, grid = 0;  // row tiles, the most of a chunk, workgroups
@@ -672,7 +673,8 @@ size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k
       // coarse: a lane's per chunk and query, 32 lanes in the 16-query tiles and 16 at most in those of
       // 128 and 256 queries, where a CU serves 128 or more queries of a chunk; more chunks than CUs only
       // where 32-bit offsets ask for them
-      const long long longest = std::max(1ll, (1ll << 30) / (256ll * row_bytes)) * 256;
+      const long long longest =
+          std::max(1ll, std::min((1ll << 30) / (256ll * row_bytes), (1ll << kChunkRowBits) / 256)) * 256;
       const long long by_len = (rows + longest - 1) / longest;
       const size_t coarse = queries <= kMaximaQueries ? (size_t)queries * 32 * (size_t)std::max<long long>(n_cus, by_len)
                                                       : (size_t)16 * std::min(queries, 512) * (size_t)n_cus +

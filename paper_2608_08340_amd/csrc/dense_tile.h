@@ -96,7 +96,8 @@ __device__ __forceinline__ void vm_wait() {
 }
 
 // Filter mode: hits wait in one LDS queue of the workgroup, (score bits << 32) | (row offset in
-// the chunk << 8) | query slot, and are moved to the queries' buffers when it fills.
+// the chunk << 8) | query slot, and are moved to the queries' buffers when it fills.  The planner
+// gives no chunk more than 2^kChunkRowBits rows.
 template <int BM, int BN>
 struct TileQueue {
   using S = TileShape<BM, BN>;
@@ -104,6 +105,7 @@ struct TileQueue {
   static constexpr int kFree = 163840 - kLds - BN * 8 - 64;
   static constexpr int CAP = kFree >= 24576 ? 3072 : 1536;  // entries
   static_assert(CAP * 8 <= kFree, "the queue fits beside the stages");
+  static_assert(BN <= 256 && kChunkRowBits + 8 <= 32, "row offset and query slot share 32 bits");
 };
 
 template <int DT, int BM, int BN, int MODE>

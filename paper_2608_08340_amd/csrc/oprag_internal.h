@@ -11,6 +11,7 @@ namespace oprag {
 
 constexpr int kMaxK = 128;                 // largest k any list may ask for
 constexpr int kMaxQPerLaunch = 4096;       // queries per dense launch (the host splits larger batches evenly)
+constexpr int kChunkRowBits = 24;          // rows of a dense chunk: a queued hit keeps its offset in so many bits
 constexpr int kDtypeF32 = 0, kDtypeBF16 = 1, kDtypeF16 = 2;
 
 // Modes of the tiled scoring kernel.
