@@ -148,8 +148,12 @@ oprag_status oprag_sparse_attach(oprag_index *idx, int32_t vocab, int64_t n_docs
 /*
  * Workspace bytes a search of nq queries needs (op: oprag_op; k_dense is the dense k for
  * OPRAG_OP_DENSE and OPRAG_OP_HYBRID and the candidate count n_cand for
- * OPRAG_OP_DENSE_FIRST, k_sparse the sparse k for OPRAG_OP_SPARSE and OPRAG_OP_HYBRID).  The value does not depend on the current row count, so a workspace
- * sized once stays valid as the index grows.
+ * OPRAG_OP_DENSE_FIRST, k_sparse the sparse k for OPRAG_OP_SPARSE and OPRAG_OP_HYBRID).  The
+ * value does not depend on the current row count, so a workspace sized once stays valid as the
+ * index grows, and a dense one serves smaller batches and smaller k as well.  With C the capacity:
+ * a dense search with k <= 16 needs at most 27 MiB for up to 64 queries (about C bytes per query
+ * before that), and at most 290 MiB for more; with k > 16 also 8 bytes per query and row
+ * for up to 32,768 rows, or per query and candidate slot (64 k of them) beyond.
  */
 oprag_status oprag_workspace_bytes(const oprag_index *idx, int32_t op, int64_t nq, int32_t k_dense, int32_t k_sparse,
                                    size_t *bytes);
@@ -174,13 +178,15 @@ oprag_status oprag_search_dense(const oprag_index *idx, const void *q_dev, int64
  * arguments, kernels and results, but no workspace argument.  The intermediate results (group
  * maxima, scores, threshold-level candidates) go to a fixed array of OPRAG_NOALLOC_SCRATCH_BYTES
  * in device memory that the library defines once per GPU and keeps until the process ends;
- * the call allocates nothing.  A k <= 16 batch (fp32: any k) that needs more runs in equal parts
- * that fit, one after another; a call returns E_CAPACITY with nothing enqueued (split the batch)
- * if 8 bytes per query and result exceed the array, or, with k > 16 on a bf16 / fp16 index, the
- * plan at the current row count does: that needs 8 bytes per query and candidate slot (every
- * row up to 32,768 rows) and can exceed the array at a few hundred queries.  Every call on one GPU shares its array, and nothing in it has to start
- * at any value (each call writes what it later reads), so calls that may overlap on one GPU
- * (different streams, or several host threads) race and must be ordered by the caller.
+ * the call allocates nothing.  Up to 64 queries with k <= 16 fit at any index length.  A larger
+ * k <= 16 batch (fp32: any k) that needs more runs in equal parts that fit, one after another.  A
+ * call returns E_CAPACITY with nothing enqueued (split the batch) if its results, at 8 bytes each, are
+ * more than the array's size, or, with k > 16 on a bf16 / fp16 index, if
+ * the plan at the current row count is: that needs 8 bytes per query and candidate slot (every
+ * row up to 32,768 rows) and can exceed the array at a few hundred queries.  Every call on one GPU
+ * shares its array, and nothing in it has to start at any value (each call writes what it later
+ * reads), so calls that may overlap on one GPU (different streams, or several host threads) race
+ * and must be ordered by the caller.
  */
 #define OPRAG_NOALLOC_SCRATCH_BYTES (32u << 20)
 oprag_status oprag_search_dense_noalloc(const oprag_index *idx, const void *q_dev, int64_t nq, int32_t k,

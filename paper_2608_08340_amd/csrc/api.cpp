@@ -134,16 +134,33 @@ size_t weighted_ws(const oprag_index* idx, int64_t nq) {
          align_up((size_t)nq * (size_t)weighted_pd(idx, nq) * 8) + align_up((size_t)nq * (size_t)weighted_pl(idx) * 8);
 }
 
-// Runs the batch in equal parts of at most max_part queries, one after another on the stream.
+// Workspace of one launch of nq queries at the current row count.
+size_t dense_ws_now(const oprag_index* idx, int64_t nq, int32_t k) {
+  nq = std::min<int64_t>(nq, (int64_t)1 << 30);
+  const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, (int)nq, k, idx->n_cus);
+  return oprag::dense_workspace_bytes(p, idx->dtype, idx->dim, (int)nq, idx->n_rows, k);
+}
+
+// Runs the batch in equal parts, one after another on the stream: as few as leave at most
+// kMaxQPerLaunch queries and at most ws_bytes of workspace to each, decided before anything is enqueued.
 oprag_status do_dense(const oprag_index* idx, const void* q, int64_t nq, int32_t k, float* scores, int64_t* ids, void* ws,
-                      size_t ws_bytes, hipStream_t s, int64_t max_part = kMaxQPerLaunch) {
+                      size_t ws_bytes, hipStream_t s) {
   const size_t es = elem_size(idx->dtype);
-  const int64_t parts = (nq + max_part - 1) / max_part, part = (nq + parts - 1) / parts;
+  int64_t parts = (nq + kMaxQPerLaunch - 1) / kMaxQPerLaunch, part = 0;
+  size_t need = 0;
+  for (;;) {
+    part = (nq + parts - 1) / parts;
+    const int64_t last = nq - (nq - 1) / part * part;  // the last part may be smaller
+    need = dense_ws_now(idx, part, k);
+    if (last != part) need = std::max(need, dense_ws_now(idx, last, k));
+    if (need <= ws_bytes) break;
+    if (part == 1)
+      return fail(OPRAG_E_CAPACITY, "one query needs %zu bytes of workspace, there are %zu", need, ws_bytes);
+    parts = std::min(nq, parts + std::max<int64_t>(1, parts / 4));
+  }
   for (int64_t q0 = 0; q0 < nq; q0 += part) {
     const int nql = (int)std::min<int64_t>(part, nq - q0);
     const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, nql, k, idx->n_cus);
-    const size_t need = oprag::dense_workspace_bytes(p, idx->dtype, idx->dim, nql, idx->n_rows, k);
-    if (need > ws_bytes) return fail(OPRAG_E_INVALID, "workspace too small: %zu < %zu bytes", ws_bytes, need);
     oprag::DenseArgs a;
     a.X = idx->slab;
     a.n_rows = idx->n_rows;
@@ -164,13 +181,6 @@ oprag_status do_dense(const oprag_index* idx, const void* q, int64_t nq, int32_t
     if (e != hipSuccess) return hip_fail(e, "dense search launch");
   }
   return OPRAG_OK;
-}
-
-// Workspace of one launch of nq queries at the current row count.
-size_t dense_ws_now(const oprag_index* idx, int64_t nq, int32_t k) {
-  nq = std::min<int64_t>(nq, (int64_t)1 << 30);
-  const oprag::DensePlan p = oprag::plan_dense(idx->dtype, idx->dim, idx->n_rows, (int)nq, k, idx->n_cus);
-  return oprag::dense_workspace_bytes(p, idx->dtype, idx->dim, (int)nq, idx->n_rows, k);
 }
 
 // The workspace of oprag_search_dense_noalloc: a fixed device array, one copy per GPU the
@@ -498,7 +508,7 @@ oprag_status oprag_search_dense(const oprag_index* idx, const void* q_dev, int64
   if (workspace_bytes < need) return fail(OPRAG_E_INVALID, "workspace too small: %zu < %zu bytes", workspace_bytes, need);
   DeviceScope ds(idx->device);
   if (ds.error() != hipSuccess) return hip_fail(ds.error(), "select device");
-  if (oprag_status st = do_dense(idx, q_dev, nq, k, scores_dev, ids_dev, workspace_dev, workspace_bytes,
+  if (oprag_status st = do_dense(idx, q_dev, nq, k, scores_dev, ids_dev, workspace_dev, need,
                                  static_cast<hipStream_t>(stream)))
     return st;
   return ok();
@@ -514,21 +524,25 @@ oprag_status oprag_search_dense_noalloc(const oprag_index* idx, const void* q_de
   if (oprag_status st = check_buf(scores_dev, "scores_dev")) return st;
   if (oprag_status st = check_buf(ids_dev, "ids_dev")) return st;
   // A bf16 / fp16 search with k > 16 keeps a candidate slot of 8 bytes per query and row (or, over
-  // long indexes, per slot) and is refused where the whole batch does not fit; any other search
-  // runs in as many parts as the array asks for.
-  int64_t part = std::min<int64_t>(nq, kMaxQPerLaunch);
-  const bool whole = k > 16 && idx->dtype != OPRAG_F32;
-  const size_t need = whole ? dense_ws_now(idx, nq, k) : (size_t)nq * k * 8;
-  if (need > kNoallocScratchBytes)
-    return fail(OPRAG_E_CAPACITY, "search needs %zu bytes of scratch, the fixed array holds %zu (fewer queries per call)",
-                need, kNoallocScratchBytes);
-  while (part > 1 && dense_ws_now(idx, part, k) > kNoallocScratchBytes) part = (part + 1) / 2;
+  // long indexes, per slot) and is refused where the whole batch does not fit.  Any other search runs
+  // in as many parts as the array asks for, one pass over the index each (up to 64 queries with k <= 16
+  // always are one part); its batches end where 8 bytes per query and result
+  // exceed the array's size.
+  if (k > 16 && idx->dtype != OPRAG_F32) {
+    const size_t need = dense_ws_now(idx, nq, k);
+    if (need > kNoallocScratchBytes)
+      return fail(OPRAG_E_CAPACITY, "search needs %zu bytes of scratch, the fixed array holds %zu (fewer queries per call)",
+                  need, kNoallocScratchBytes);
+  } else if ((size_t)nq * k * 8 > kNoallocScratchBytes) {
+    return fail(OPRAG_E_CAPACITY, "%lld queries with k = %d are more than one call without a workspace takes (fewer queries per call)",
+                (long long)nq, k);
+  }
   DeviceScope ds(idx->device);
   if (ds.error() != hipSuccess) return hip_fail(ds.error(), "select device");
   void* ws = nullptr;
   if (oprag_status st = scratch_of(idx->device, &ws)) return st;
   if (oprag_status st = do_dense(idx, q_dev, nq, k, scores_dev, ids_dev, ws, kNoallocScratchBytes,
-                                 static_cast<hipStream_t>(stream), part))
+                                 static_cast<hipStream_t>(stream)))
     return st;
   return ok();
 }

@@ -482,6 +482,9 @@ __global__ void clear_ints_kernel(int* p, long long n, const int* gate) {
 // Planning.
 // ------------------------------------------------------------------------------------
 constexpr int kMaximaQueries = 64;  // k <= 16: up to this many queries group maxima at any length
+// Most bytes of a launch's group maxima: of up to 64 queries (so that any index length fits the fixed
+// array of the search without a workspace), and of larger batches.
+constexpr size_t kMaximaBytes = 24ull << 20, kBatchMaximaBytes = 256ull << 20;
 
 // Tile shapes of dense_tile.h.  eff: the rate of the shape's MFMAs at 1,024 queries over 32,768 x
 // 1,024 bf16 rows, relative to the largest (1,285 TFLOP/s; 1,088, 1,079, 920 and 671 for the
@@ -549,7 +552,8 @@ int pick_shape(int dtype, int d, long long rows, int nq, int n_cus) {
   int best = -1;
   double cost = 0.0;
   for (int i = 0; i < (dtype == kDtypeF32 ? kNumShapes32 : kNumShapes); ++i) {
-    if (nq > kMaximaQueries && kShapes[i].mt < 4) continue;  // (the groups' bound relies on it)
+    // (the bounds of the groups' memory rely on it; for up to 64 queries the larger tiles never cost less)
+    if ((nq > kMaximaQueries) != (kShapes[i].mt >= 4)) continue;
     const TileGrid g = tile_grid(i, dtype, d, rows, nq, n_cus);
     const double rounds = (double)((g.grid + n_cus - 1) / n_cus);
     const double c = rounds * (double)g.most * kShapes[i].bm * kShapes[i].bn /
@@ -571,18 +575,39 @@ long long maxima_group(int dtype, int d, long long rows, int k) {
   return g;
 }
 
-// The maxima of a launch with groups of G rows (or as many as a lane has of a tile).
-MaxGroups max_groups(int shape, int dtype, int d, long long rows, int nq, int n_cus, long long G) {
+// The maxima of a launch with groups of G rows (or as many as a lane has of a tile); unit_sh > 0: of
+// all that a lane has of 1 << unit_sh tiles.
+MaxGroups max_groups(int shape, int dtype, int d, long long rows, int nq, int n_cus, long long G, int unit_sh = 0) {
   const ShapeInfo& sh = kShapes[shape];
   const TileGrid g = tile_grid(shape, dtype, d, rows, nq, n_cus);
   MaxGroups m;
-  m.gs = (int)std::min<long long>(G / 4, sh.mt);
+  m.gs = unit_sh > 0 ? sh.mt : (int)std::min<long long>(G / 4, sh.mt);
   m.per_tile = sh.wm * 4 * (sh.mt / m.gs);
-  m.count = rows > 0 ? (int)(g.tiles * m.per_tile) : 0;
+  m.unit_sh = unit_sh;
+  m.upc = unit_sh > 0 ? (int)((g.most + (1ll << unit_sh) - 1) >> unit_sh) : 0;
+  m.count = rows > 0 ? (int)((unit_sh > 0 ? (long long)g.n_chunks * m.upc : g.tiles) * m.per_tile) : 0;
   m.ld = (m.count + 3) & ~3ll;
   m.coarse = rows > 0 ? g.n_chunks * sh.wm * 4 : 0;
   m.cld = (m.coarse + 3) & ~3ll;
   return m;
+}
+
+// The maxima of a k <= 16 search: groups of maxima_group rows, and larger ones while they take more
+// memory than they may.  Writing fewer of them is faster as well: 8.45 M rows of 384 fp16, 64 queries, 2.00 ms
+// with 8 rows a group (271 MB), 1.37 with 128 (17 MB); 16 queries, 1.52 ms with 4 rows (135 MB), 1.11 with 32.
+MaxGroups search_groups(int shape, int dtype, int d, long long rows, int nq, int k, int n_cus) {
+  const bool small = nq <= kMaximaQueries;
+  long long G = maxima_group(dtype, d, rows, k);
+  int unit_sh = 0;
+  for (;;) {
+    MaxGroups m = max_groups(shape, dtype, d, rows, nq, n_cus, G, unit_sh);
+    const bool fits = (size_t)nq * (size_t)m.ld * 4 <= (small ? kMaximaBytes : kBatchMaximaBytes);
+    if (fits || (m.gs == kShapes[shape].mt && (!small || m.upc == 1))) return m;
+    if (m.gs < kShapes[shape].mt)
+      G = 8 * m.gs;
+    else
+      ++unit_sh;
+  }
 }
 
 bool use_maxima(long long rows, int nq, int k) { return k <= 16 && (nq <= kMaximaQueries || rows <= kMaximaRows); }
@@ -614,7 +639,7 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
   p.shape = pick_shape(dtype, d, n_rows, nq, n_cus);
   p.kind = use_maxima(n_rows, nq, k) ? DensePlan::kMaxima : (use_dump(n_rows, k) ? DensePlan::kDump : DensePlan::kFilter);
   if (p.kind == DensePlan::kMaxima) {
-    p.groups = max_groups(p.shape, dtype, d, n_rows, nq, n_cus, maxima_group(dtype, d, n_rows, k));
+    p.groups = search_groups(p.shape, dtype, d, n_rows, nq, k, n_cus);
     if (p.groups.count <= kOneLevel && nq <= 2 * n_cus) p.groups.coarse = p.groups.cld = 0;
   } else if (p.kind == DensePlan::kDump) {
     p.ld = (n_rows + 3) & ~3ll;
@@ -659,35 +684,39 @@ size_t dense_workspace_bytes(const DensePlan& p, int dtype, int d, int nq, long 
   return filter_body(nq, k) + 256;
 }
 
+// The caller splits a batch until every part fits this.  A workspace for nq queries and k results
+// serves every smaller batch and k.
 size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k, int n_cus) {
-  size_t b = 0;
-  if (k <= 16) {
-    // The most groups any row count up to `rows` is split into: at the last row count of each group
-    // size (tiles of more than 64 queries allow groups of 16, smaller ones may have only 4 rows)
-    const long long row_bytes = (long long)d * elem_bytes(dtype);
-    auto maxima = [&](int queries, long long rows) {
-      long long groups = 0;
-      const long long top = queries <= kMaximaQueries ? 4 : std::min(16ll, maxima_group(dtype, d, rows, k));
-      for (long long g = 4; g <= top; g *= 2)
-        groups = std::max(groups, ((g == top ? rows : std::min(rows, g * g * k * row_bytes / 2)) + g - 1) / g + 64);
-      // coarse: a lane's per chunk and query, 32 lanes in the 16-query tiles and 16 at most in those of
-      // 128 and 256 queries, where a CU serves 128 or more queries of a chunk; more chunks than CUs only
-      // where 32-bit offsets ask for them
-      const long long longest =
-          std::max(1ll, std::min((1ll << 30) / (256ll * row_bytes), (1ll << kChunkRowBits) / 256)) * 256;
-      const long long by_len = (rows + longest - 1) / longest;
-      const size_t coarse = queries <= kMaximaQueries ? (size_t)queries * 32 * (size_t)std::max<long long>(n_cus, by_len)
-                                                      : (size_t)16 * std::min(queries, 512) * (size_t)n_cus +
-                                                            (size_t)queries * 16 * (size_t)by_len;
-      return maxima_bytes(queries, (groups + 3) & ~3ll, 0) + align_up256(coarse * 4 + (size_t)queries * 16);
-    };
-    b = maxima(std::min(nq, kMaximaQueries), capacity);  // a smaller batch fits too
-    if (nq > kMaximaQueries) {
-      b = std::max(b, maxima(nq, std::min(capacity, kMaximaRows)));
-      if (capacity > kMaximaRows) b = std::max(b, filter_body(nq, k) + 256);
-    }
-  } else {
-    b = dump_bytes(nq, std::min(capacity, kDumpRows));
+  const long long row_bytes = (long long)d * elem_bytes(dtype);
+  const int k1 = std::min(k, 16);  // of maxima; larger k: of k = 16
+  // The most groups any row count up to `rows` is split into: at the last row count of each group
+  // size (tiles of more than 64 queries allow groups of 16, smaller ones may have only 4 rows)
+  auto maxima = [&](int queries, long long rows) {
+    const bool small = queries <= kMaximaQueries;
+    long long groups = 0;
+    const long long top = small ? 4 : std::min(16ll, maxima_group(dtype, d, rows, k1));
+    for (long long g = 4; g <= top; g *= 2)
+      groups = std::max(groups, ((g == top ? rows : std::min(rows, g * g * k1 * row_bytes / 2)) + g - 1) / g + 64);
+    // coarse: a lane's per chunk and query, 32 lanes in the 16-query tiles and 16 at most in those of
+    // 128 and 256 queries, where a CU serves 128 or more queries of a chunk; more chunks than CUs only
+    // where 32-bit offsets ask for them
+    const long long longest =
+        std::max(1ll, std::min((1ll << 30) / (256ll * row_bytes), (1ll << kChunkRowBits) / 256)) * 256;
+    const long long by_len = (rows + longest - 1) / longest;
+    const size_t coarse = 4 * (small ? (size_t)queries * 32 * (size_t)std::max<long long>(n_cus, by_len)
+                                     : (size_t)16 * std::min(queries, 512) * (size_t)n_cus +
+                                           (size_t)queries * 16 * (size_t)by_len);
+    const size_t most = small ? std::max(kMaximaBytes, coarse) : kBatchMaximaBytes;  // (small: a unit per chunk at least)
+    const size_t fine = std::min((size_t)queries * (size_t)((groups + 3) & ~3ll) * 4, most);
+    return align_up256(fine) + align_up256(coarse + (size_t)queries * 16);
+  };
+  size_t b = maxima(std::min(nq, kMaximaQueries), capacity);
+  if (nq > kMaximaQueries) {
+    b = std::max(b, maxima(nq, std::min(capacity, kMaximaRows)));
+    if (capacity > kMaximaRows) b = std::max(b, filter_body(nq, k1) + 256);
+  }
+  if (k > 16) {
+    b = std::max(b, dump_bytes(nq, std::min(capacity, kDumpRows)));
     if (capacity > kDumpRows) b = std::max(b, filter_body(nq, k) + 256);
   }
   return b;
@@ -714,12 +743,14 @@ hipError_t launch_maxima(int dtype, int shape, const MaxGroups& m, const DenseAr
   arg.mx = m.count > 0 ? reinterpret_cast<float*>(a.partial) : nullptr;
   arg.mx_ld = m.ld;
   arg.mx_gs = m.gs;
+  arg.unit_sh = m.unit_sh;
+  arg.upc = m.upc;
   arg.cmx = m.coarse > 0 ? reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.partial) +
                                                     align_up256((size_t)a.nq * (size_t)m.ld * 4))
                          : nullptr;
   arg.cmx_ld = m.cld;
   arg.gate = gate;
-  return launch_tiles(dtype, shape, kTileMax, arg, rows, n_cus, s, ev0, ev1);
+  return launch_tiles(dtype, shape, m.unit_sh > 0 ? kTileUnits : kTileMax, arg, rows, n_cus, s, ev0, ev1);
 }
 
 hipError_t launch_rescore(int dtype, int shape, const MaxGroups& m, const DenseArgs& a, int n_cus, const int* gate,
@@ -750,6 +781,8 @@ hipError_t launch_rescore(int dtype, int shape, const MaxGroups& m, const DenseA
   r.gl_sh = log2i(sh.mt / m.gs);
   r.gs_sh = log2i(m.gs);
   r.mt_sh = log2i(sh.mt);
+  r.unit_sh = m.unit_sh;
+  r.upc = m.upc;
   r.out_scores = a.out_scores;
   r.out_ids = a.out_ids;
   r.gate = gate;

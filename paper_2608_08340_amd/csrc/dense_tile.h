@@ -114,6 +114,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   using M = Mfma<DT>;
   using V = typename M::V;
   using S = TileShape<BM, BN>;
+  constexpr bool MAX = MODE == kTileMax || MODE == kTileUnits, UNITS = MODE == kTileUnits;
   constexpr int MP = S::MP, MS = S::MS, NP = S::NP, NS = S::NS, NBUF = S::NBUF;
   constexpr int MT = MP * MS, NT = NP * NS;          // subtiles per wave
   constexpr int AI = BM / MP / 64;            // load instructions per wave and part: rows,
@@ -282,6 +283,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
     // The epilogue of a (row part, query part) of the finished tile: acc[i][j][r] is row
     // tile0 + 16 (MT wm + i) + 4 (lane / 16) + r against query slot qn0 + 16 j.
     long long tile0 = row_begin;
+    [[maybe_unused]] const long long unit0 = chunk * a.upc;  // UNITS: the chunk's first
     bool full = false;                                // every row of the tile exists (uniform)
     [[maybe_unused]] f32x4 mq, mw[8];                 // MAX, MT 1: the lane's maxima of 4 tiles, of 32
     int lim = 0, t = 0;                               // row 16 i + r of the lane exists iff < lim
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
 #pragma unroll
       for (int jj = 0; jj < NS; ++jj) {
         const int j = PB * NS + jj, q = q0 + qn0 + j * 16;
-        if constexpr (MODE == kTileMax) {
+        if constexpr (MAX) {
           // m[i]: the largest score of subtile i's rows, NaN where none exists
           float m[MS];
 #pragma unroll
@@ -311,20 +313,30 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
           for (int i = 0; i < MS; ++i) x = __builtin_fmaxf(x, m[i]);
           dmx[j] = x;
           if constexpr (MT == 1) {
-            // One group per lane and tile.  A store makes the counted waits after it wait for its
-            // reply (2.7 us a time: 16 queries over 1 M x 1,024 rows, 374 us with a store in every
-            // fourth tile, 355 now), so the maxima of 32 tiles are kept and leave together, the four
-            // lanes of a query exchanging them for 16 bytes of one tile each.
+            // One group per lane and tile (or unit of tiles).  A store makes the counted waits after it wait
+            // for its reply (2.7 us a time: 16 queries over 1 M x 1,024 rows, 374 us with a store in every
+            // fourth tile, 355 now), so the maxima of 32 units are kept and leave together, the four
+            // lanes of a query exchanging them for 16 bytes of one unit each.
             static_assert(NT == 1);
+            const int s = UNITS ? t >> a.unit_sh : t;  // the tile or unit, in the chunk and in all
+            const long long unit = UNITS ? unit0 + s : tile0 / BM;
+            float g = m[0];                            // the group so far
+            bool whole = true;                         // (workgroup-uniform) the unit ends here
+            if constexpr (UNITS) {
+              const int um = (1 << a.unit_sh) - 1;
+              if ((t & um) != 0) g = __builtin_fmaxf(dmn[0], g);
+              dmn[0] = g;
+              whole = t == n_tiles - 1 || (t & um) == um;
+            }
             if (n_tiles == 1) {  // workgroup-uniform: nothing to wait for later, and little code to fetch
               if (a.mx != nullptr && q < a.nq)
-                a.mx[(long long)q * a.mx_ld + (tile0 / BM) * (S::WM * 4) + wm * 4 + (lane >> 4)] = m[0];
-            } else {
-              const int e = t & 3, tq = (t >> 2) & 7;
-              mq[0] = e == 0 ? m[0] : mq[0];
-              mq[1] = e == 1 ? m[0] : mq[1];
-              mq[2] = e == 2 ? m[0] : mq[2];
-              mq[3] = e == 3 ? m[0] : mq[3];
+                a.mx[(long long)q * a.mx_ld + unit * (S::WM * 4) + wm * 4 + (lane >> 4)] = g;
+            } else if (whole) {
+              const int e = s & 3, tq = (s >> 2) & 7;
+              mq[0] = e == 0 ? g : mq[0];
+              mq[1] = e == 1 ? g : mq[1];
+              mq[2] = e == 2 ? g : mq[2];
+              mq[3] = e == 3 ? g : mq[3];
               const bool end = t == n_tiles - 1;
               if (a.mx != nullptr && (e == 3 || end)) {
 #pragma unroll
@@ -332,11 +344,11 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
                   if (tq == u) mw[u] = mq;
                 if (end || (tq == 7 && e == 3)) {
                   const int h = lane >> 4;
-                  float* dst = a.mx + (long long)q * a.mx_ld + (tile0 / BM - (t & 31)) * (S::WM * 4) + wm * 4;
+                  float* dst = a.mx + (long long)q * a.mx_ld + (unit - (s & 31)) * (S::WM * 4) + wm * 4;
 #pragma unroll
                   for (int u = 0; u < 8; ++u) {
-                    if (4 * u > (t & 31)) break;
-                    float y[4];  // from lane h ^ o of the query, for tile 4 u + h
+                    if (4 * u > (s & 31)) break;
+                    float y[4];  // from lane h ^ o of the query, for unit 4 u + h
 #pragma unroll
                     for (int o = 0; o < 4; ++o) {
                       const int c = h ^ o;
@@ -349,12 +361,19 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
                       const int c = h ^ r;
                       v[r] = c & 2 ? (c & 1 ? y[3] : y[2]) : (c & 1 ? y[1] : y[0]);
                     }
-                    if (q < a.nq && 4 * u + h <= (t & 31))
+                    if (q < a.nq && 4 * u + h <= (s & 31))
                       *reinterpret_cast<f32x4*>(dst + (long long)(4 * u + h) * (S::WM * 4)) = v;
                   }
                 }
               }
             }
+          } else if constexpr (UNITS) {
+            static_assert(MT == 2 && MP == 1);
+            const int um = (1 << a.unit_sh) - 1;
+            const float y = __builtin_fmaxf(m[0], m[1]);
+            dmn[j] = (t & um) == 0 ? y : __builtin_fmaxf(dmn[j], y);
+            if ((t == n_tiles - 1 || (t & um) == um) && q < a.nq)
+              a.mx[(long long)q * a.mx_ld + (unit0 + (t >> a.unit_sh)) * (S::WM * 4) + wm * 4 + (lane >> 4)] = dmn[j];
           } else if (a.mx != nullptr && q < a.nq) {
             // the lane's groups of a query are consecutive: MT / gs of them, MS / gs in this part
             // (gs 8: one for both parts)
@@ -563,6 +582,17 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
       }
     }
     finish();
+    if constexpr (UNITS) {
+      // a chunk with a unit less than upc: no rows there
+      if (((n_tiles - 1) >> a.unit_sh) + 1 < a.upc) {  // workgroup-uniform
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          const int q = q0 + qn0 + j * 16;
+          if (q < a.nq)
+            a.mx[(long long)q * a.mx_ld + (unit0 + a.upc - 1) * (S::WM * 4) + wm * 4 + (lane >> 4)] = __builtin_nanf("");
+        }
+      }
+    }
 #undef OPRAG_MUL
 #undef OPRAG_RDA
 #undef OPRAG_RDB
@@ -627,7 +657,7 @@ constexpr int kReCand = 64;                              // groups ranked by a w
 constexpr int kReList = 256;                             // groups scored: k + the groups of one tile
 constexpr int kReRows = 1024;                            // rows ranked together
 
-template <int DT>
+template <int DT, bool UNITS>
 __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
   if (a.gate != nullptr && *a.gate == 0) return;
   using M = Mfma<DT>;
@@ -746,18 +776,20 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
     }
   }
   __syncthreads();
-  const int tb_sh = a.gpt_sh;   // groups of a tile (or, coarse, of a chunk): 1 << gpt_sh
+  const int tb_sh = a.gpt_sh;   // groups of a tile (or unit of tiles, or, coarse, of a chunk): 1 << gpt_sh
   const int lanes_sh = a.lanes_sh, gl_sh = a.gl_sh;
   // chunk * tiles / n_chunks, in 32 bits
   auto first_tile = [&](int chunk) { return chunk * a.least + (int)((unsigned)(chunk * a.spare) / (unsigned)a.n_chunks); };
   if (two) {
-    const int nh = s_nh, per = a.most << gl_sh;  // groups of a lane over its chunk
+    const int nh = s_nh, per = (UNITS ? a.upc : a.most) << gl_sh;  // groups of a lane over its chunk
     if (nh <= kReCand)
       for (int p = t; p < nh * per; p += NT) {
         const int c = clist[p / per], u = p % per, chunk = c >> lanes_sh, l = c & ((1 << lanes_sh) - 1);
-        const int tile = first_tile(chunk) + (u >> gl_sh);
-        if (tile < first_tile(chunk + 1)) {
-          const int g = (tile << tb_sh) + (l << gl_sh) + (u & ((1 << gl_sh) - 1));
+        const int unit0 = UNITS ? chunk * a.upc : first_tile(chunk);  // tiles or units
+        const int end = UNITS ? unit0 + a.upc : first_tile(chunk + 1);
+        const int unit = unit0 + (u >> gl_sh);
+        if (unit < end) {
+          const int g = (unit << tb_sh) + (l << gl_sh) + (u & ((1 << gl_sh) - 1));
           offer(groups[g], g);
         }
       }
@@ -826,7 +858,7 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
   }
   __syncthreads();  // every wave has read the candidates
   // 5. score the rows of the listed groups, 16 rows per wave and step, and keep the k best
-  const int g_rows = by_chunk ? (4 << a.mt_sh) * a.most : 4 << a.gs_sh;  // rows of a group
+  const int g_rows = by_chunk ? (4 << a.mt_sh) * a.most : 4 << (UNITS ? a.gs_sh + a.unit_sh : a.gs_sh);  // rows of a group
   const int total = nl * g_rows;  // (of distinct rows)
   const int nks = (rowb + 127) / 128 * 2;      // 64-byte steps
   const unsigned char* X = static_cast<const unsigned char*>(a.X);
@@ -839,6 +871,12 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
       l = rem >> gl_sh;
       sub += (rem & ((1 << gl_sh) - 1)) << a.gs_sh;
       tile = g >> tb_sh;
+      if constexpr (UNITS) {
+        const int chunk = tile / a.upc;
+        tile = first_tile(chunk) + ((tile - chunk * a.upc) << a.unit_sh) + (sub >> a.mt_sh);
+        sub &= (1 << a.mt_sh) - 1;
+        if (tile >= first_tile(chunk + 1)) return a.n_rows;
+      }
     } else {
       const int chunk = g >> lanes_sh;
       l = g & ((1 << lanes_sh) - 1);
@@ -963,7 +1001,8 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
   if (shape == I)                                                              \
     fn = mode == kTileMax    ? dense_tile_kernel<DT, BM, BN, kTileMax>         \
          : mode == kTileFilt ? dense_tile_kernel<DT, BM, BN, kTileFilt>        \
-                             : dense_tile_kernel<DT, BM, BN, kTileDump>;
+         : mode == kTileDump ? dense_tile_kernel<DT, BM, BN, kTileDump>        \
+                             : nullptr;
   OPRAG_TILE(0, 128, 16)
   OPRAG_TILE(1, 128, 64)
   OPRAG_TILE(2, 128, 128)
@@ -972,6 +1011,10 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
     OPRAG_TILE(4, 128, 256)
     OPRAG_TILE(5, 256, 256)
   }
+  if (mode == kTileUnits)
+    fn = shape == 0   ? dense_tile_kernel<DT, 128, 16, kTileUnits>
+         : shape == 1 ? dense_tile_kernel<DT, 128, 64, kTileUnits>
+                      : nullptr;
 #undef OPRAG_TILE
   if (fn == nullptr) return hipErrorInvalidValue;
   void* params[] = {&arg};
@@ -985,7 +1028,10 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
 template <int DT>
 hipError_t rescore_launch(const RescoreArgs& a, int nq, hipStream_t s) {
   const size_t lds = (size_t)a.d * (DT == kDtypeF32 ? 4 : 2);
-  hipLaunchKernelGGL(rescore_kernel<DT>, dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
+  if (a.unit_sh > 0)
+    hipLaunchKernelGGL((rescore_kernel<DT, true>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
+  else
+    hipLaunchKernelGGL((rescore_kernel<DT, false>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
   return hipGetLastError();
 }
 

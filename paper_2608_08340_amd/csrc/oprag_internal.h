@@ -14,8 +14,8 @@ constexpr int kMaxQPerLaunch = 4096;       // queries per dense launch (the host
 constexpr int kChunkRowBits = 24;          // rows of a dense chunk: a queued hit keeps its offset in so many bits
 constexpr int kDtypeF32 = 0, kDtypeBF16 = 1, kDtypeF16 = 2;
 
-// Modes of the tiled scoring kernel.
-enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2 };
+// Modes of the tiled scoring kernel (kTileUnits: kTileMax with groups that span tiles).
+enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2, kTileUnits = 3 };
 
 struct DenseArgs {
   const void* X;                // slab rows [n_rows x d]
@@ -47,27 +47,32 @@ struct DenseArgs {
   float* dump = nullptr;
   long long dump_ld = 0;
   float* dump_mm = nullptr;
-  // Group maxima: the largest score of each group (a lane's rows of mx_gs consecutive 16-row subtiles)
-  // to mx[q * mx_ld + group], and of each lane over its chunk to cmx[q * cmx_ld + ..] (NaN: no row;
+  // Group maxima: the largest score of each group (a lane's rows of mx_gs consecutive 16-row subtiles;
+  // kTileUnits: of all its subtiles in a unit of 1 << unit_sh consecutive tiles of a chunk) to
+  // mx[q * mx_ld + group], and of each lane over its chunk to cmx[q * cmx_ld + ..] (NaN: no row;
   // either may be null).
   float* mx = nullptr;
   long long mx_ld = 0;
   int mx_gs = 1;
+  int unit_sh = 0, upc = 0;     // upc units per chunk (the last of a chunk may be short or empty)
   float* cmx = nullptr;
   long long cmx_ld = 0;
 };
 
-// Maxima of one launch: groups of gs subtiles (a power of two), per_tile of a row tile, count in all;
-// coarse ones in all (0: none are kept).  The groups' row stride ld, the coarse ones' cld.
+// Maxima of one launch: groups of gs subtiles (a power of two), per_tile of a row tile (of a unit of
+// tiles, DenseArgs), count in all; coarse ones in all (0: none are kept).  The groups' row stride ld,
+// the coarse ones' cld.
 struct MaxGroups {
   int gs = 1, per_tile = 0, count = 0, coarse = 0;
+  int unit_sh = 0, upc = 0;
   long long ld = 0, cld = 0;
 };
 
 // The k best rows from a launch's maxima (gate as above).  Lane l of a tile (wave row and lane
 // quarter, 1 << lanes_sh of them) has 1 << mt_sh subtiles in groups of 1 << gs_sh (1 << gl_sh of them);
 // group ((tile << lanes_sh) + l << gl_sh) + i, coarse maximum (chunk << lanes_sh) + l, and chunk
-// c has tiles [c tiles / n_chunks, (c + 1) tiles / n_chunks), at most `most`.
+// c has tiles [c tiles / n_chunks, (c + 1) tiles / n_chunks), at most `most`.  With unit_sh > 0 unit
+// c upc + u, of the tiles 1 << unit_sh from the u-th such run of the chunk, takes a tile's place.
 struct RescoreArgs {
   const void* X = nullptr;
   const void* Q = nullptr;
@@ -83,6 +88,7 @@ struct RescoreArgs {
   int tile_rows = 0, n_chunks = 1, most = 0;
   int least = 0, spare = 0;      // tiles / n_chunks, tiles % n_chunks
   int gpt_sh = 0, lanes_sh = 0, gl_sh = 0, gs_sh = 0, mt_sh = 0;
+  int unit_sh = 0, upc = 0;
   float* out_scores = nullptr;
   long long* out_ids = nullptr;
   const int* gate = nullptr;

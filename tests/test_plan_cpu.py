@@ -52,3 +52,35 @@ def test_chunk_rows_fit_a_queued_hit(tmp_path):
         CHECK((rows + p.n_chunks - 1) / p.n_chunks <= (1 << 24), "d %d rows %lld nq %d: %d chunks", d, rows, nq, p.n_chunks)
       }
 """)
+
+
+def test_workspace_bound_holds_and_stays_small(tmp_path):
+    """A workspace sized for a batch, k and capacity serves every smaller batch, k and row count, and
+    group maxima never take more than 24 MiB of it for up to 64 queries (with the coarse ones less than the
+    32 MiB of the fixed array) nor 256 MiB for more, however long the index."""
+    _run(tmp_path, r"""
+  std::mt19937_64 g(7);
+  auto log_int = [&](double lo, double hi) {
+    return (long long)std::exp(std::uniform_real_distribution<double>(std::log(lo), std::log(hi))(g));
+  };
+  for (int i = 0; i < 300000; ++i) {
+    const int dtype = (int)(g() % 3);
+    const int d = dtype == kDtypeF32 ? 4 * (int)log_int(1, 2048) : 128 * (int)log_int(1, 64);
+    const long long cap = std::min<long long>(log_int(1, 2147483646), 288000000000ll / (d * (dtype == kDtypeF32 ? 4 : 2)));
+    const long long rows = g() % 4 ? std::min(cap, log_int(1, (double)cap + 1)) : cap;
+    const int nq_ws = (int)log_int(1, 4096), nq = g() % 2 ? nq_ws : (int)log_int(1, nq_ws + 1);
+    const int k_ws = (int)log_int(1, 128), k = g() % 2 ? k_ws : (int)log_int(1, k_ws + 1);
+    const size_t bound = dense_workspace_bound(dtype, d, cap, nq_ws, k_ws, kCus);
+    // as the host runtime splits a batch
+    auto need = [&](int n) { return dense_workspace_bytes(plan_dense(dtype, d, rows, n, k, kCus), dtype, d, n, rows, k); };
+    int parts = 1, part = nq;
+    for (; std::max(need(part), need(nq - (nq - 1) / part * part)) > bound; part = (nq + parts - 1) / parts) {
+      CHECK(part > 64, "dtype %d d %d cap %lld rows %lld nq %d/%d k %d/%d: %zu > %zu", dtype, d, cap, rows, nq, nq_ws, k, k_ws,
+            need(part), bound)
+      parts += std::max(1, parts / 4);
+    }
+    CHECK(parts <= 4, "%d parts: dtype %d d %d rows %lld nq %d k %d", parts, dtype, d, rows, nq, k)
+    if (nq <= 64 && k <= 16) CHECK(need(nq) <= (size_t)OPRAG_SCRATCH, "%zu bytes: dtype %d d %d rows %lld nq %d k %d", need(nq), dtype, d, rows, nq, k)
+    if (k_ws <= 16) CHECK(bound <= (nq_ws <= 64 ? 27u : 290u) << 20, "%zu bytes: d %d cap %lld nq %d k %d", bound, d, cap, nq_ws, k_ws)
+  }
+""".replace("OPRAG_SCRATCH", "(32u << 20)"))
