@@ -180,8 +180,8 @@ oprag_status oprag_search_dense(const oprag_index *idx, const void *q_dev, int64
  * in device memory that the library defines once per GPU and keeps until the process ends;
  * the call allocates nothing.  Up to 64 queries with k <= 16 fit at any index length.  A larger
  * k <= 16 batch (fp32: any k) that needs more runs in equal parts that fit, one after another.  A
- * call returns E_CAPACITY with nothing enqueued (split the batch) if its results, at 8 bytes each, are
- * more than the array's size, or, with k > 16 on a bf16 / fp16 index, if
+ * call returns E_CAPACITY with nothing enqueued (split the batch) if its results, of 2^20 queries at
+ * most and at 8 bytes each, are more than the array's size, or, with k > 16 on a bf16 / fp16 index, if
  * the plan at the current row count is: that needs 8 bytes per query and candidate slot (every
  * row up to 32,768 rows) and can exceed the array at a few hundred queries.  Every call on one GPU
  * shares its array, and nothing in it has to start at any value (each call writes what it later

@@ -526,14 +526,14 @@ oprag_status oprag_search_dense_noalloc(const oprag_index* idx, const void* q_de
   // A bf16 / fp16 search with k > 16 keeps a candidate slot of 8 bytes per query and row (or, over
   // long indexes, per slot) and is refused where the whole batch does not fit.  Any other search runs
   // in as many parts as the array asks for, one pass over the index each (up to 64 queries with k <= 16
-  // always are one part); its batches end where 8 bytes per query and result
+  // always are one part); its batches end where 8 bytes per query and result (of 2^20 queries at most)
   // exceed the array's size.
   if (k > 16 && idx->dtype != OPRAG_F32) {
     const size_t need = dense_ws_now(idx, nq, k);
     if (need > kNoallocScratchBytes)
       return fail(OPRAG_E_CAPACITY, "search needs %zu bytes of scratch, the fixed array holds %zu (fewer queries per call)",
                   need, kNoallocScratchBytes);
-  } else if ((size_t)nq * k * 8 > kNoallocScratchBytes) {
+  } else if ((size_t)std::min<int64_t>(nq, (int64_t)1 << 20) * k * 8 > kNoallocScratchBytes) {
     return fail(OPRAG_E_CAPACITY, "%lld queries with k = %d are more than one call without a workspace takes (fewer queries per call)",
                 (long long)nq, k);
   }

@@ -67,6 +67,20 @@ def test_without_a_workspace_past_33_million_rows(nq):
     idx.close()
 
 
+def test_without_a_workspace_more_than_2_to_20_queries():
+    """Calls of any batch up to 2^20 queries' worth of 8 bytes per result stay accepted, and past it those
+    that were: k = 4 and 2^20 + 5 queries.  One more result each is refused, with nothing enqueued."""
+    nq, k = (1 << 20) + 5, 4
+    log("noalloc large batch")
+    idx, X, Q = _index(5, 300, 4, nq, "f32", 100)
+    sc, ids = idx.search_dense_noalloc(Q, k)
+    _check(X, Q, k, sc, ids, [0, 4095, 4096, nq // 2, nq - 1])
+    from paper_2608_08340_amd import OpragError
+    with pytest.raises(OpragError, match="one call"):
+        idx.search_dense_noalloc(Q, k + 1)
+    idx.close()
+
+
 @pytest.mark.parametrize("n,nq,k", [(33_000, 70, 17), (150_001, 70, 40), (150_001, 3, 100)])
 def test_fp32_levels(n, nq, k):
     """fp32 with k > 16 past 32,768 rows: threshold levels."""
