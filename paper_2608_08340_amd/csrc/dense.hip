@@ -8,9 +8,12 @@
 //    best groups of a query are found and their rows scored again (rescore_kernel);
 //  - k > 16, up to 32,768 rows: every score; one workgroup per query selects from its score row;
 //  - otherwise (k > 16, or more than 64 queries over a long index): threshold levels over growing
-//    row prefixes.  The first level's group maxima give each query a lower bound of its k-th
-//    score over the prefix; the next level collects only the rows that reach it, whose k-th
-//    score is the next threshold; the last level is the whole index.
+//    shares of the rows.  The first level's group maxima give each query a lower bound of its k-th
+//    score; the next level collects only the rows that reach it, whose k-th score is the next
+//    threshold; the last level completes the index.  Every level's rows are spread over the index:
+//    rows come in the order in which documents were ingested, and with levels over prefixes a topic of
+//    more adjacent rows than a buffer holds overflowed it (1 M x 768 bf16, 1,024 queries, k = 10: rows
+//    in topics of 4,096, 6.5 ms by prefixes and 1.27 spread out; in random order 1.30 and 1.31).
 #include <algorithm>
 #include <type_traits>
 
@@ -82,6 +85,9 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(const void* __restrict_
   __syncthreads();
   if (t == 0 && !(threshold_only && !SCORES) && ccnt != nullptr) ccnt[q] = 0;  // every thread has read it: the next pass starts from zero
   const int need = min(k, n);
+  // A level with fewer than k keys so far (the rows behind the last threshold may be in later levels): that
+  // threshold stays.
+  if (!SCORES && threshold_only && need < k) return;  // workgroup-uniform
   const bool in_reg = !SCORES && n <= kRegKeys * NT;  // workgroup-uniform
   // Register keys: thread t holds keys ib + NT u, where ib puts the first 256 keys in 256
   // different groups, so at least min(n, 256) >= need groups are nonempty.  Of scores only the maximum
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(const void* __restrict_
     }
     if (threshold_only) {
       // An earlier level only hands its k-th score on as the next threshold, and tau is a
-      // valid one: at least k keys reach it (k <= n here, else the next level takes all rows).
+      // valid one: at least k keys reach it.
       const float f = SCORES ? ftau : (tau != 0ull ? comp_score(tau) : kNegInf);
       if (t == 0) out_scores[(long long)q * k + (k - 1)] = need == k ? f : kNegInf;
       return;
@@ -510,7 +516,10 @@ constexpr long long kFilterFirst = 32000;     // most rows of the first level
 // Row growth between levels.  A level's hits cost its tiles time in proportion (at 16-fold growth and k
 // = 100, a hit in 5,000 scores, a fifth of it), a level itself two launches.
 constexpr long long filter_grow(int k) { return k <= 16 ? 8 : 4; }
-constexpr long long kSmallCap = 2048;         // filter, k <= 16: candidate slots per query
+// Filter, k <= 16: candidate slots per query.  A query whose best rows no level but the first and the last
+// has (a topic between two tiles) collects about 64 k, 1,024 at k = 16, and half as many again one time in a
+// few thousand at 2,048 slots.
+constexpr long long kSmallCap = 3072;
 
 size_t align_up256(size_t x) { return (x + 255) & ~(size_t)255; }
 int elem_bytes(int dtype) { return dtype == kDtypeF32 ? 4 : 2; }
@@ -520,11 +529,22 @@ int log2i(long long x) {
   return l;
 }
 
+// The row tiles of a launch (DenseArgs): all of the index, or some of them.
+struct TileSet {
+  long long tiles, tile_pitch;
+  int row_pitch = 1, skip = 0;
+};
+TileSet all_tiles(const ShapeInfo& sh, long long rows) { return {std::max(1ll, (rows + sh.bm - 1) / sh.bm), sh.bm}; }
+
+constexpr long long kChunkBytes = 1ll << 30;
+
 // Most row tiles of a chunk: 32-bit byte offsets reach past it, and its row offsets fit the
 // kChunkRowBits bits that a queued hit has for them (fp32 rows of up to 12 dimensions are the ones
 // short enough for that to count).
-long long max_tiles(const ShapeInfo& sh, int dtype, int d) {
-  return std::max(1ll, std::min((1ll << 30) / ((long long)sh.bm * d * elem_bytes(dtype)), (1ll << kChunkRowBits) / sh.bm));
+long long max_tiles(const ShapeInfo& sh, int dtype, int d, const TileSet& set) {
+  long long by_offset = kChunkBytes / (set.tile_pitch * d * elem_bytes(dtype));
+  if (set.skip > 0) by_offset = by_offset * set.skip / (set.skip + 1);
+  return std::max(1ll, std::min(by_offset, (1ll << kChunkRowBits) / sh.bm));
 }
 
 // Chunks of one launch: row tiles divided as evenly as they go over at most one workgroup per CU
@@ -534,26 +554,30 @@ struct TileGrid {
   long long tiles = 0, most = 0, grid = 0;  // row tiles, the most of a chunk, workgroups
 };
 
-TileGrid tile_grid(int shape, int dtype, int d, long long rows, int nq, int n_cus) {
+TileGrid tile_grid(int shape, int dtype, int d, const TileSet& set, int nq, int n_cus) {
   const ShapeInfo& sh = kShapes[shape];
   TileGrid g;
   g.n_qblocks = (nq + sh.bn - 1) / sh.bn;
-  g.tiles = std::max(1ll, (rows + sh.bm - 1) / sh.bm);
-  const long long chunks = std::max(1ll, (long long)n_cus / g.n_qblocks), mt = max_tiles(sh, dtype, d);
+  g.tiles = set.tiles;
+  const long long chunks = std::max(1ll, (long long)n_cus / g.n_qblocks), mt = max_tiles(sh, dtype, d, set);
   g.n_chunks = (int)std::min(g.tiles, std::max(chunks, (g.tiles + mt - 1) / mt));
   g.most = (g.tiles + g.n_chunks - 1) / g.n_chunks;
   g.grid = (long long)g.n_chunks * g.n_qblocks;
   return g;
 }
+TileGrid tile_grid(int shape, int dtype, int d, long long rows, int nq, int n_cus) {
+  return tile_grid(shape, dtype, d, all_tiles(kShapes[shape], rows), nq, n_cus);
+}
 
 // The shape whose slowest CU finishes its MFMAs first.  (A short index or a small batch wants small
-// tiles, so that every CU has one; the padding of the last query block counts too.)
-int pick_shape(int dtype, int d, long long rows, int nq, int n_cus) {
+// tiles, so that every CU has one; the padding of the last query block counts too.)  bm: only among the
+// shapes with so many rows a tile.
+int pick_shape(int dtype, int d, long long rows, int nq, int n_cus, int bm = 0) {
   int best = -1;
   double cost = 0.0;
   for (int i = 0; i < (dtype == kDtypeF32 ? kNumShapes32 : kNumShapes); ++i) {
     // (the bounds of the groups' memory rely on it; for up to 64 queries the larger tiles never cost less)
-    if ((nq > kMaximaQueries) != (kShapes[i].mt >= 4)) continue;
+    if ((nq > kMaximaQueries) != (kShapes[i].mt >= 4) || (bm != 0 && bm != kShapes[i].bm)) continue;
     const TileGrid g = tile_grid(i, dtype, d, rows, nq, n_cus);
     const double rounds = (double)((g.grid + n_cus - 1) / n_cus);
     const double c = rounds * (double)g.most * kShapes[i].bm * kShapes[i].bn /
@@ -644,23 +668,36 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
   } else if (p.kind == DensePlan::kDump) {
     p.ld = (n_rows + 3) & ~3ll;
   } else {
-    // Levels from the end: each prefix holds a fixed share of the next one's rows, down to a
-    // first level of at most kFilterFirst.
-    long long back[16];
+    // Levels from the end: each holds a fixed share of the next one's tiles, every 4th or 8th of them,
+    // down to a first level of at most kFilterFirst rows.
+    const int bm = kShapes[p.shape].bm;
+    const long long tiles = (n_rows + bm - 1) / bm;
+    long long back[16], rows = n_rows;
     int nb = 0;
-    back[nb++] = n_rows;
-    while (nb < 15) {
-      const long long r = std::max(kFilterMin, (back[nb - 1] + filter_grow(k) - 1) / filter_grow(k));
-      back[nb++] = r;
-      if (r <= kFilterFirst) break;
+    for (long long stride = 1; nb < 15; stride *= filter_grow(k)) {
+      back[nb++] = stride;
+      rows = std::max(kFilterMin, (rows + filter_grow(k) - 1) / filter_grow(k));
+      if (rows <= kFilterFirst) break;
     }
-    p.n_levels = nb;
-    for (int l = 0; l < nb; ++l) p.level_rows[l] = back[nb - 1 - l];
+    p.n_levels = nb + 1;
+    for (int l = 1; l <= nb; ++l) {
+      p.level_pitch[l] = back[nb - l] * bm;
+      p.level_rows[l] = std::min(n_rows, (tiles + back[nb - l] - 1) / back[nb - l] * bm);
+    }
+    // The first level only hands thresholds on, so its rows need not be among the second one's: single rows
+    // spread over the index (an odd number apart: of documents of 2^n rows not always the same one), in
+    // tiles as long as 32-bit offsets allow.
+    p.shape0 = pick_shape(dtype, d, std::min(rows, n_rows), nq, n_cus);
+    const int bm0 = kShapes[p.shape0].bm;
+    const long long tiles0 = std::min(rows, n_rows) / bm0;
+    p.level_pitch[0] = n_rows / tiles0;
+    p.row_pitch0 = (int)std::min(p.level_pitch[0] / bm0, kChunkBytes / ((long long)bm0 * d * elem_bytes(dtype)));
+    p.row_pitch0 -= p.row_pitch0 % 2 == 0 ? 1 : 0;
+    p.level_rows[0] = tiles0 * bm0;
     // the first level's groups, as many as their memory and one pass of the selection allow: the k best
     // rows then mostly fall in groups of their own, and the k-th maximum is close to the k-th score
     p.cap = filter_cap(k);
     const long long most = std::min(2 * p.cap, 8192ll);
-    p.shape0 = pick_shape(dtype, d, p.level_rows[0], nq, n_cus);
     for (long long G = 4; G <= 32; G *= 2) {
       p.groups = max_groups(p.shape0, dtype, d, p.level_rows[0], nq, n_cus, G);
       if (p.groups.count <= most) break;
@@ -724,11 +761,14 @@ size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k
 
 namespace {
 
-hipError_t launch_tiles(int dtype, int shape, int mode, const DenseArgs& a, long long rows, int n_cus, hipStream_t s,
+hipError_t launch_tiles(int dtype, int shape, int mode, const DenseArgs& a, const TileSet& set, int n_cus, hipStream_t s,
                         hipEvent_t ev0, hipEvent_t ev1) {
-  const TileGrid g = tile_grid(shape, dtype, a.d, rows, a.nq, n_cus);
+  const TileGrid g = tile_grid(shape, dtype, a.d, set, a.nq, n_cus);
   DenseArgs arg = a;
-  arg.n_rows = rows;
+  arg.tile_pitch = (int)set.tile_pitch;
+  arg.row_pitch = set.row_pitch;
+  arg.skip = set.skip;
+  arg.skip_recip = set.skip > 0 ? (unsigned)(((1ull << 32) + set.skip - 1) / set.skip) : 0u;
   arg.n_qblocks = g.n_qblocks;
   arg.n_chunks = g.n_chunks;
   arg.tiles = g.tiles;
@@ -737,7 +777,7 @@ hipError_t launch_tiles(int dtype, int shape, int mode, const DenseArgs& a, long
   return tile_launch<kDtypeF32>(shape, mode, g.grid, arg, s, ev0, ev1);
 }
 
-hipError_t launch_maxima(int dtype, int shape, const MaxGroups& m, const DenseArgs& a, long long rows, int n_cus,
+hipError_t launch_maxima(int dtype, int shape, int mode, const MaxGroups& m, const DenseArgs& a, const TileSet& set, int n_cus,
                          const int* gate, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   DenseArgs arg = a;
   arg.mx = m.count > 0 ? reinterpret_cast<float*>(a.partial) : nullptr;
@@ -750,7 +790,7 @@ hipError_t launch_maxima(int dtype, int shape, const MaxGroups& m, const DenseAr
                          : nullptr;
   arg.cmx_ld = m.cld;
   arg.gate = gate;
-  return launch_tiles(dtype, shape, m.unit_sh > 0 ? kTileUnits : kTileMax, arg, rows, n_cus, s, ev0, ev1);
+  return launch_tiles(dtype, shape, mode, arg, set, n_cus, s, ev0, ev1);
 }
 
 hipError_t launch_rescore(int dtype, int shape, const MaxGroups& m, const DenseArgs& a, int n_cus, const int* gate,
@@ -821,7 +861,8 @@ hipError_t launch_select_scores(const float* scores, int n, long long ld, int* c
 hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipStream_t s, hipEvent_t ev0,
                         hipEvent_t ev1) {
   if (p.kind == DensePlan::kMaxima) {
-    const hipError_t e = launch_maxima(dtype, p.shape, p.groups, a, a.n_rows, p.n_cus, nullptr, s, ev0, ev1);
+    const hipError_t e = launch_maxima(dtype, p.shape, p.groups.unit_sh > 0 ? kTileUnits : kTileMax, p.groups, a,
+                                       all_tiles(kShapes[p.shape], a.n_rows), p.n_cus, nullptr, s, ev0, ev1);
     if (e != hipSuccess) return e;
     return launch_rescore(dtype, p.shape, p.groups, a, p.n_cus, nullptr, s);
   }
@@ -829,7 +870,8 @@ hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipSt
     DenseArgs arg = a;
     arg.dump = reinterpret_cast<float*>(a.partial);
     arg.dump_ld = p.ld;
-    const hipError_t e = launch_tiles(dtype, p.shape, kTileDump, arg, a.n_rows, p.n_cus, s, ev0, ev1);
+    const hipError_t e = launch_tiles(dtype, p.shape, kTileDump, arg, all_tiles(kShapes[p.shape], a.n_rows), p.n_cus, s,
+                                      ev0, ev1);
     if (e != hipSuccess) return e;
     return launch_select_scores(arg.dump, (int)a.n_rows, p.ld, nullptr, a.nq, a.k, a.out_scores, a.out_ids, false, s);
   }
@@ -844,7 +886,8 @@ hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipSt
   hipLaunchKernelGGL(clear_ints_kernel, dim3(1), dim3(64), 0, s, fl, 4ll, nullptr);
   // The first level's thresholds (its selection also zeroes the counts); out_scores[q k + k - 1]
   // holds a query's threshold between the levels.
-  hipError_t e = launch_maxima(dtype, p.shape0, p.groups, a, p.level_rows[0], p.n_cus, nullptr, s, nullptr, nullptr);
+  hipError_t e = launch_maxima(dtype, p.shape0, kTileSample, p.groups, a, {p.level_rows[0] / kShapes[p.shape0].bm, p.level_pitch[0],
+                                                                p.row_pitch0}, p.n_cus, nullptr, s, nullptr, nullptr);
   if (e == hipSuccess)
     e = launch_select_scores(reinterpret_cast<const float*>(a.partial),
                              p.groups.count, p.groups.ld, ccnt, a.nq, a.k, a.out_scores,
@@ -855,21 +898,25 @@ hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipSt
   arg.cbuf = a.partial;
   arg.ccnt = ccnt;
   arg.cap = p.cap;
-  const size_t row_bytes = (size_t)a.d * elem_bytes(dtype);
+  const int bm = kShapes[p.shape].bm;
+  const TileSet all = all_tiles(kShapes[p.shape], a.n_rows);
   for (int l = 1; l < p.n_levels && e == hipSuccess; ++l) {
     const bool last = l == p.n_levels - 1;
-    // The first level's rows are scored again here; later levels take the rows past the previous
-    // one's and add to its candidates.
-    const long long from = l == 1 ? 0 : p.level_rows[l - 1], rows = p.level_rows[l] - from;
-    const int shape = last ? p.shape : pick_shape(dtype, a.d, rows, a.nq, p.n_cus);
-    arg.X = static_cast<const unsigned char*>(a.X) + (size_t)from * row_bytes;
-    arg.row_base = from;
+    // Level 1 has every tile of its pitch; later levels take those that the ones before left out and add to
+    // their candidates.
+    auto of_pitch = [&](long long pitch) { return (all.tiles + pitch / bm - 1) / (pitch / bm); };
+    TileSet set{of_pitch(p.level_pitch[l]), p.level_pitch[l]};
+    if (l > 1) {
+      set.skip = (int)(p.level_pitch[l - 1] / p.level_pitch[l]) - 1;
+      set.tiles -= of_pitch(p.level_pitch[l - 1]);
+    }
+    const int shape = last ? p.shape : pick_shape(dtype, a.d, set.tiles * bm, a.nq, p.n_cus, bm);
     // A tile expects its scores times k / (the previous level's rows) hits: the queue is looked at
     // before they can fill half of it, every 16 tiles at most.
     const double hits = (double)kShapes[shape].bm * kShapes[shape].bn * a.k / (double)p.level_rows[l - 1];
     arg.check_mask = 15;
     while (arg.check_mask > 0 && (arg.check_mask + 1) * hits > 512.0) arg.check_mask >>= 1;
-    e = launch_tiles(dtype, shape, kTileFilt, arg, rows, p.n_cus, s, last ? ev0 : nullptr, last ? ev1 : nullptr);
+    e = launch_tiles(dtype, shape, kTileFilt, arg, set, p.n_cus, s, last ? ev0 : nullptr, last ? ev1 : nullptr);
     if (e == hipSuccess)
       e = launch_select(p.n_cus, arg.cbuf, ccnt, p.cap, a.nq, a.k, a.out_scores, a.out_ids, last ? fl : nullptr, nullptr,
                         !last, s);
@@ -881,15 +928,13 @@ hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipSt
   // their k-th scores are valid thresholds and no lower), and if that overflows too, group
   // maxima over the whole index answer.  Each repair launch returns at once when its flag is
   // clear.
-  arg.X = a.X;
-  arg.row_base = 0;
   arg.check_mask = 0;
   arg.gate = fl;
-  e = launch_tiles(dtype, p.shape, kTileFilt, arg, a.n_rows, p.n_cus, s, nullptr, nullptr);
+  e = launch_tiles(dtype, p.shape, kTileFilt, arg, all, p.n_cus, s, nullptr, nullptr);
   if (e == hipSuccess)
     e = launch_select(p.n_cus, arg.cbuf, ccnt, p.cap, a.nq, a.k, a.out_scores, a.out_ids, fl + 2, fl, false, s);
   if (e == hipSuccess)
-    e = launch_maxima(dtype, p.shape, p.groups_all, a, a.n_rows, p.cus_all, fl + 2, s, nullptr, nullptr);
+    e = launch_maxima(dtype, p.shape, kTileMax, p.groups_all, a, all, p.cus_all, fl + 2, s, nullptr, nullptr);
   if (e == hipSuccess) e = launch_rescore(dtype, p.shape, p.groups_all, a, p.cus_all, fl + 2, s);
   return e;
 }
@@ -907,14 +952,14 @@ int dense_dump_chunks(int dtype, int d, long long capacity, int nq, int n_cus) {
   long long most = 1;
   for (int i = 0; i < kNumShapes; ++i) {
     const ShapeInfo& sh = kShapes[i];
-    const long long tiles = (capacity + sh.bm - 1) / sh.bm, mu = max_tiles(sh, dtype, d);
+    const long long tiles = (capacity + sh.bm - 1) / sh.bm, mu = max_tiles(sh, dtype, d, all_tiles(sh, capacity));
     most = std::max(most, std::min(tiles, std::max((long long)n_cus / ((nq + sh.bn - 1) / sh.bn), (tiles + mu - 1) / mu)));
   }
   return (int)most;
 }
 
 hipError_t launch_dense_dump(const DensePlan& p, int dtype, const DenseArgs& a, hipStream_t s) {
-  return launch_tiles(dtype, p.shape, kTileDump, a, a.n_rows, p.n_cus, s, nullptr, nullptr);
+  return launch_tiles(dtype, p.shape, kTileDump, a, all_tiles(kShapes[p.shape], a.n_rows), p.n_cus, s, nullptr, nullptr);
 }
 
 hipError_t launch_weighted_fuse(int n_cus, const float* D, const float* B, long long ld, long long n, long long n_lex, int nq,

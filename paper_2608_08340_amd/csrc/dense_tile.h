@@ -95,8 +95,8 @@ __device__ __forceinline__ void vm_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Filter mode: hits wait in one LDS queue of the workgroup, (score bits << 32) | (row offset in
-// the chunk << 8) | query slot, and are moved to the queries' buffers when it fills.  The planner
+// Filter mode: hits wait in one LDS queue of the workgroup, (score bits << 32) | (row of the
+// chunk's, counted over its tiles, << 8) | query slot, and are moved to the queries' buffers when it fills.  The planner
 // gives no chunk more than 2^kChunkRowBits rows.
 template <int BM, int BN>
 struct TileQueue {
@@ -114,7 +114,8 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   using M = Mfma<DT>;
   using V = typename M::V;
   using S = TileShape<BM, BN>;
-  constexpr bool MAX = MODE == kTileMax || MODE == kTileUnits, UNITS = MODE == kTileUnits;
+  constexpr bool UNITS = MODE == kTileUnits, SAMPLE = MODE == kTileSample;
+  constexpr bool MAX = MODE == kTileMax || UNITS || SAMPLE;
   constexpr int MP = S::MP, MS = S::MS, NP = S::NP, NS = S::NS, NBUF = S::NBUF;
   constexpr int MT = MP * MS, NT = NP * NS;          // subtiles per wave
   constexpr int AI = BM / MP / 64;            // load instructions per wave and part: rows,
@@ -145,9 +146,25 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   const int q0 = qb * BN;
   const int rowb = a.d * (DT == kDtypeF32 ? 4 : 2);  // bytes of a row
   const int nkt = max(2, (rowb + 127) / 128);        // 128-byte stages per tile
-  const long long row_begin = chunk * a.tiles / a.n_chunks * BM;
-  const long long row_end = min((chunk + 1) * a.tiles / a.n_chunks * BM, a.n_rows);
-  const int n_tiles = (int)((row_end - row_begin + BM - 1) / BM);  // 0 for an empty chunk
+  // The chunk has tiles j0 .. j0 + n_tiles - 1 of the launch's (DenseArgs).
+  constexpr bool SKIPS = MODE == kTileFilt;
+  const int j0 = (int)(chunk * a.tiles / a.n_chunks);
+  const int n_tiles = a.n_rows > 0 ? (int)((chunk + 1) * a.tiles / a.n_chunks) - j0 : 0;
+  const int tile_pitch = SKIPS || SAMPLE ? a.tile_pitch : BM, row_pitch = SAMPLE ? a.row_pitch : 1;
+  auto tile_row = [&](unsigned j) __attribute__((always_inline)) {  // the first row of tile j
+    if constexpr (SKIPS) j += __umulhi(j, a.skip_recip) + (a.skip > 0 ? 1u : 0u);
+    return (unsigned)tile_pitch * j;
+  };
+  const long long row_begin = tile_row(j0);
+  const long long row_end = min((long long)tile_row(j0 + max(n_tiles, 1) - 1) + BM * row_pitch, a.n_rows);
+  // Row of the index, from the tile's first, at position r of the tile.  SAMPLE: similar rows, which are
+  // often neighbours, go to groups of their own (a lane's four positions are a quarter of the tile apart, those
+  // of its next subtile an eighth).  The bits of r count separately.
+  auto row_at = [&](int r) __attribute__((always_inline)) {
+    if constexpr (SAMPLE)
+      return ((r & 3) * (BM / 4) + (r >> 4 & 1) * (BM / 8) + (r >> 5) * 4 + (r >> 2 & 3)) * row_pitch;
+    return r;
+  };
 
   const int qn0 = wn * NT * 16 + (lane & 15);  // this lane's queries
   float dmn[NT], dmx[NT];
@@ -176,43 +193,49 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
     // A load moves eight 128-byte rows; its lane l reads piece (l % 8) ^ swizzle of row l / 8.
     // Load j of wave w fills LDS rows 64 j + 8 w .. + 7 of its part.
     const int lofs = (lane >> 3) * rowb + (((lane & 7) ^ (4 * (w & 1) + (lane >> 4))) * 16);
+    const int xofs = lofs + (row_at(lane >> 3) - (lane >> 3)) * rowb;  // of the index's rows
     const unsigned ldsw = lds0 + w * 1024;
     // fp32 rows may end inside a stage: past the row a lane's offset is out of range (reads 0)
     const int cpiece = ((lane & 7) ^ (4 * (w & 1) + (lane >> 4))) * 16;
-    auto at = [&](int off, int k) __attribute__((always_inline)) {
-      if constexpr (DT == kDtypeF32) return k + cpiece < rowb ? lofs + off : -1;
-      return lofs + off;
+    auto at = [&](int lane_ofs, int off, int k) __attribute__((always_inline)) {
+      if constexpr (DT == kDtypeF32) return k + cpiece < rowb ? lane_ofs + off : -1;
+      return lane_ofs + off;
     };
     int arow[AI], brow[BI];  // byte offset of the first of those rows (part 0) in the tile / block
 #pragma unroll
     for (int j = 0; j < AI; ++j) {
       const int r = j * 64 + w * 8;
-      arow[j] = ((r / (MS * 16)) * (MT * 16) + r % (MS * 16)) * rowb;
+      arow[j] = row_at((r / (MS * 16)) * (MT * 16) + r % (MS * 16)) * rowb;
     }
 #pragma unroll
     for (int j = 0; j < BI; ++j) {
       const int r = j * 64 + w * 8;
       brow[j] = ((r / (NS * 16)) * (NT * 16) + r % (NS * 16)) * rowb;
     }
-    const int apart = MS * 16 * rowb, bpart = NS * 16 * rowb;
-    const int tile_bytes = BM * rowb, kend = nkt * 128;
+    const int apart = row_at(MS * 16) * rowb, bpart = NS * 16 * rowb;
+    const int kend = nkt * 128;
+    // Byte offset of the chunk's tile i.  (Past the chunk it may wrap, of a single tile's chunk and a very
+    // long pitch: such loads land inside the chunk again and are never used.)
+    auto tile_ofs = [&](int i) __attribute__((always_inline)) {
+      return (tile_row((unsigned)(j0 + i)) - (unsigned)row_begin) * (unsigned)rowb;
+    };
     // Cursors (byte offsets of the next stage to load): x for the parts loaded LA stages ahead,
-    // y (MP 2) for the second parts, one stage ahead.  Past the chunk nothing is read.
-    int xk = 0, xt = 0, yk = 0, yt = 0;
-#define OPRAG_ADV(K, T) \
-  {                     \
-    K += 128;           \
-    if (K == kend) {    \
-      K = 0;            \
-      T += tile_bytes;  \
-    }                   \
+    // y (MP 2) for the second parts, one stage ahead.  Past the chunk nothing is read.  Each goes on to its
+    // next tile (at xn, yn) once while a tile is multiplied.
+    int xk = 0, yk = 0;
+    unsigned xt = 0u, yt = 0u, xn = 0u, yn = 0u;
+#define OPRAG_ADV(K, T, N)       \
+  {                              \
+    K += 128;                    \
+    T = K == kend ? N : T;       \
+    K = K == kend ? 0 : K;       \
   }
 #define OPRAG_LDA(P, K, T, BO)                                                     \
   _Pragma("unroll") for (int j = 0; j < AI; ++j)                                   \
-      lds_load16(rx, at((T) + (K) + (P) * apart + arow[j], K), ldsw + (BO) + (P) * RAP + j * 8192);
+      lds_load16(rx, at(xofs, (T) + (K) + (P) * apart + arow[j], K), ldsw + (BO) + (P) * RAP + j * 8192);
 #define OPRAG_LDB(P, K, BO)                                                        \
   _Pragma("unroll") for (int j = 0; j < BI; ++j)                                   \
-      lds_load16(rq, at((K) + (P) * bpart + brow[j], K), ldsw + (BO) + RB + (P) * RBP + j * 8192);
+      lds_load16(rq, at(lofs, (K) + (P) * bpart + brow[j], K), ldsw + (BO) + RB + (P) * RBP + j * 8192);
 
     // fragment addresses: row (lane % 16) of the wave's first subtile, pieces 4 s + lane / 16
     const int sw = (lane >> 1) & 7;
@@ -228,16 +251,17 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
     auto start = [&]() __attribute__((always_inline)) {
       nxt = LA % NBUF * BUF;
       cur1 = 0;
+      xn = yn = tile_ofs(1);
       if constexpr (MP == 2) {
         OPRAG_LDA(0, xk, xt, 0)
         OPRAG_LDB(0, xk, 0)
-        OPRAG_ADV(xk, xt)
+        OPRAG_ADV(xk, xt, xn)
         OPRAG_LDB(1, yk, 0)
         OPRAG_LDA(1, yk, yt, 0)
-        OPRAG_ADV(yk, yt)
+        OPRAG_ADV(yk, yt, yn)
         OPRAG_LDA(0, xk, xt, BUF)
         OPRAG_LDB(0, xk, BUF)
-        OPRAG_ADV(xk, xt)
+        OPRAG_ADV(xk, xt, xn)
         vm_wait<2 * AI + 2 * BI>();
       } else {
 #pragma unroll
@@ -245,7 +269,8 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
           OPRAG_LDA(0, xk, xt, u * BUF)
           OPRAG_LDB(0, xk, u * BUF)
           if constexpr (NP == 2) OPRAG_LDB(1, xk, u * BUF)
-          OPRAG_ADV(xk, xt)
+          OPRAG_ADV(xk, xt, xn)
+          if (xk == 0) xn = tile_ofs((u + 1) / nkt + 1);
         }
         if constexpr (NP == 2)
           vm_wait<AI + 3 * BI>();
@@ -286,8 +311,9 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   __builtin_amdgcn_sched_barrier(0);
 
     // The epilogue of a (row part, query part) of the finished tile: acc[i][j][r] is row
-    // tile0 + 16 (MT wm + i) + 4 (lane / 16) + r against query slot qn0 + 16 j.
-    long long tile0 = row_begin;
+    // tile0 + 16 (MT wm + i) + 4 (lane / 16) + r against query slot qn0 + 16 j (tile0 = row_begin + trow).
+    int trow = 0;                                     // the tile's first row, from row_begin
+    const int rows = (int)(row_end - row_begin);
     [[maybe_unused]] const long long unit0 = chunk * a.upc;  // UNITS: the chunk's first
     bool full = false;                                // every row of the tile exists (uniform)
     [[maybe_unused]] f32x4 mq, mw[8];                 // MAX, MT 1: the lane's maxima of 4 tiles, of 32
@@ -325,7 +351,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
             // lanes of a query exchanging them for 16 bytes of one unit each.
             static_assert(NT == 1);
             const int s = UNITS ? t >> a.unit_sh : t;  // the tile or unit, in the chunk and in all
-            const long long unit = UNITS ? unit0 + s : tile0 / BM;
+            const long long unit = UNITS ? unit0 + s : j0 + t;
             float g = m[0];                            // the group so far
             bool whole = true;                         // (workgroup-uniform) the unit ends here
             if constexpr (UNITS) {
@@ -384,7 +410,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
             // the lane's groups of a query are consecutive: MT / gs of them, MS / gs in this part
             // (gs 8: one for both parts)
             const int gs = a.mx_gs, gl = MT / gs;  // launch-uniform
-            float* dst = a.mx + (long long)q * a.mx_ld + (tile0 / BM) * (S::WM * 4 * gl) + (wm * 4 + (lane >> 4)) * gl +
+            float* dst = a.mx + (long long)q * a.mx_ld + (long long)(j0 + t) * (S::WM * 4 * gl) + (wm * 4 + (lane >> 4)) * gl +
                          (gs <= MS ? PA * (MS / gs) : 0);
             if (gs == 1) {
               if constexpr (MS == 4)
@@ -410,7 +436,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
             a.cmx[(long long)q * a.cmx_ld + chunk * (S::WM * 4) + (wm * 4 + (lane >> 4))] = x;
         } else if constexpr (MODE == kTileDump) {
           if (q < a.nq) {
-            float* dst = a.dump + (long long)q * a.dump_ld + tile0 + row0;
+            float* dst = a.dump + (long long)q * a.dump_ld + row_begin + trow + row0;
 #pragma unroll
             for (int i = PA * MS; i < (PA + 1) * MS; ++i) {
               if (full || i * 16 + 3 < lim) {
@@ -465,13 +491,13 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
             float x = y[0];
             if constexpr (MS >= 2) x = b & 4 ? y[1] : y[0];
             if constexpr (MS == 4) x = b & 8 ? (b & 4 ? y[3] : y[2]) : x;
-            const unsigned row = (unsigned)(t * BM + row0 + PA * MS * 16 + (b >> 2) * 16 + (b & 3));  // in the chunk
+            const unsigned row = (unsigned)(row0 + PA * MS * 16 + (b >> 2) * 16 + (b & 3));  // in the tile
             if (pos < Q::CAP) {
-              queue[pos] = ((u64)__float_as_uint(x) << 32) | (u64)((row << 8) | (unsigned)(qn0 + j * 16));
+              queue[pos] = ((u64)__float_as_uint(x) << 32) | (u64)(((unsigned)(t * BM) + row) << 8 | (unsigned)(qn0 + j * 16));
             } else {  // the queue is full until the next flush: straight to the query's buffer
               const long long g = atomicAdd(a.ccnt + q, 1);
               if (g < a.cap)
-                a.cbuf[(long long)q * a.cap + g] = composite(x, (uint32_t)(a.row_base + row_begin + row));
+                a.cbuf[(long long)q * a.cap + g] = composite(x, (uint32_t)row_begin + (uint32_t)trow + row);
               else
                 qth[qn0 + j * 16] = __builtin_inff();
             }
@@ -494,13 +520,13 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
         OPRAG_MUL(0, 0, (2 * AI + 2 * BI))
         OPRAG_RDB(1)
         OPRAG_LDA(1, yk, yt, oth)
-        OPRAG_ADV(yk, yt)
+        OPRAG_ADV(yk, yt, yn)
         OPRAG_MUL(0, 1, (2 * AI + 2 * BI))
         OPRAG_RDA(1)
         OPRAG_LDA(0, xk, xt, cur)
         OPRAG_MUL(1, 1, (2 * AI + 2 * BI))
         OPRAG_LDB(0, xk, cur)
-        OPRAG_ADV(xk, xt)
+        OPRAG_ADV(xk, xt, xn)
         OPRAG_MUL(1, 0, (2 * AI + 2 * BI))
       } else {
         const int cur = cur1;
@@ -512,10 +538,10 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
           OPRAG_MUL(0, 0, (2 * AI + 3 * BI))
           OPRAG_RDB(1)
           OPRAG_LDB(1, xk, nxt)
-          OPRAG_ADV(xk, xt)
+          OPRAG_ADV(xk, xt, xn)
           OPRAG_MUL(0, 1, (AI + 3 * BI))
         } else {
-          OPRAG_ADV(xk, xt)
+          OPRAG_ADV(xk, xt, xn)
           OPRAG_MUL(0, 0, ((LA - 1) * (AI + BI)))
         }
         cur1 = cur == (NBUF - 1) * BUF ? 0 : cur + BUF;
@@ -523,7 +549,10 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
       }
     };
     start();
+    const int ahead = LA / nkt;  // the tile that x has reached when the first one is multiplied
     for (; t < n_tiles; ++t) {
+      xn = tile_ofs(t + ahead + 1);
+      if constexpr (MP == 2) yn = tile_ofs(t + 1);
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -536,9 +565,9 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
       } else {
         for (int k = 0; k < nkt; ++k) stage(I0);
       }
-      tile0 = row_begin + (long long)t * BM;
-      full = tile0 + BM <= row_end;
-      lim = (int)min((long long)BM, row_end - tile0) - row0;
+      trow = (int)(tile_row((unsigned)(j0 + t)) - (unsigned)row_begin);
+      full = trow + BM <= rows;
+      lim = min(BM, rows - trow) - row0;
       if constexpr (MODE == kTileFilt) {
 #pragma unroll
         for (int j = 0; j < NT; ++j) th[j] = qth[qn0 + j * 16];
@@ -585,7 +614,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
                 if (g < a.cap)
                   a.cbuf[(long long)(q0 + slot) * a.cap + g] =
                       composite(__uint_as_float((unsigned)(x >> 32)),
-                                (uint32_t)(a.row_base + row_begin + ((unsigned)x >> 8)));
+                                tile_row(j0 + ((unsigned)x >> 8) / BM) + ((unsigned)x >> 8) % BM);
               }
             }
             lds_barrier();
@@ -1017,6 +1046,7 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
     fn = mode == kTileMax    ? dense_tile_kernel<DT, BM, BN, kTileMax>         \
          : mode == kTileFilt ? dense_tile_kernel<DT, BM, BN, kTileFilt>        \
          : mode == kTileDump ? dense_tile_kernel<DT, BM, BN, kTileDump>        \
+         : mode == kTileSample ? dense_tile_kernel<DT, BM, BN, kTileSample>    \
                              : nullptr;
   OPRAG_TILE(0, 128, 16)
   OPRAG_TILE(1, 128, 64)

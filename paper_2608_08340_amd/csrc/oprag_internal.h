@@ -14,8 +14,9 @@ constexpr int kMaxQPerLaunch = 4096;       // queries per dense launch (the host
 constexpr int kChunkRowBits = 24;          // rows of a dense chunk: a queued hit keeps its offset in so many bits
 constexpr int kDtypeF32 = 0, kDtypeBF16 = 1, kDtypeF16 = 2;
 
-// Modes of the tiled scoring kernel (kTileUnits: kTileMax with groups that span tiles).
-enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2, kTileUnits = 3 };
+// Modes of the tiled scoring kernel (kTileUnits: kTileMax with groups that span tiles; kTileSample: of
+// rows spread over the index).
+enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2, kTileUnits = 3, kTileSample = 4 };
 
 struct DenseArgs {
   const void* X;                // slab rows [n_rows x d]
@@ -27,6 +28,12 @@ struct DenseArgs {
   int n_qblocks;
   int n_chunks;
   long long tiles;              // chunk c takes row tiles [c tiles / n_chunks, (c + 1) tiles / n_chunks)
+  // kTileSample, kTileFilt: tile j of the launch starts at row j tile_pitch (otherwise its tiles are the
+  // index's).  kTileSample: a tile's rows are row_pitch apart.  kTileFilt with skip > 0: tile j starts at
+  // row (j + j / skip + 1) tile_pitch, so every (skip + 1)-th is left out (skip_recip: 2^32 / skip,
+  // rounded up).
+  int tile_pitch = 0, row_pitch = 1, skip = 0;
+  unsigned skip_recip = 0;
   unsigned long long* partial;  // workspace
   float* out_scores;            // [nq x k]
   long long* out_ids;           // [nq x k]
@@ -39,7 +46,6 @@ struct DenseArgs {
   int* ccnt = nullptr;
   long long cap = 0;
   int check_mask = 0;
-  long long row_base = 0;       // id of row 0 of X
   // When set, the launch does nothing unless *gate != 0 (a device-side overflow flag).
   const int* gate = nullptr;
   // Score dump: every score to dump[q * dump_ld + row]; with dump_mm set, also the minimum and
@@ -113,7 +119,9 @@ struct DensePlan {
   // kFilter
   int shape0 = 0;               // tile shape of the first level
   int n_levels = 0;
-  long long level_rows[16] = {};
+  long long level_pitch[16] = {};    // rows from a tile of a level to the next
+  int row_pitch0 = 1;                // and between the rows of the first level's tiles
+  long long level_rows[16] = {};     // rows of the level and those before it
   long long cap = 0;            // candidate slots per query
   MaxGroups groups_all;         // exact fallback: coarse maxima over all rows,
   int cus_all = 0;              // in as many chunks as this many CUs would get

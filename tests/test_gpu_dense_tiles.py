@@ -53,9 +53,9 @@ def test_threshold_levels(n, nq, k):
 @pytest.mark.parametrize("case", ["ascending", "ties"])
 @pytest.mark.parametrize("nq,k", [(70, 5), (300, 16)])
 def test_levels_overflow_and_repair(case, nq, k):
-    """"ascending": scores grow with the row id, so every prefix's threshold admits all later rows and
-    the buffers overflow; "ties": a quarter of the rows share the top score, so the repair
-    overflows too and the group maxima of the whole index answer."""
+    """"ascending": scores grow with the row id, in steps of 1,600 equal ones; "ties": a quarter of the
+    rows share the top score, so the buffers overflow, the repair's as well, and the group maxima of the
+    whole index answer."""
     log("overflow", case, nq, k)
     n, d = 400_000, 128
     r = np.arange(n)
@@ -68,6 +68,75 @@ def test_levels_overflow_and_repair(case, nq, k):
     Q[:, 0] = 4.0
     Q[:, 1] = np.arange(nq) % 2
     _check(X, Q, k, "bf16", samp=np.r_[0:4, nq - 1])
+
+
+def _overflowed(idx, nq, k):
+    """The first flag of the levels' workspace: 0 unless a candidate buffer overflowed (which costs
+    another pass over the index).  It lies behind the buffers and the counts, 256-byte aligned."""
+    cap = 3072 if k <= 16 else max(4096, 64 * k)
+    at = nq * cap * 8 + (nq * 4 + 255) // 256 * 256
+    return int(idx._ws[at:at + 4].view(torch.int32).item())
+
+
+@pytest.mark.parametrize("nq,k", [(70, 10), (300, 16), (1000, 5), (70, 60)])
+@pytest.mark.parametrize("run", [1500, 5000, 40_000])
+@pytest.mark.parametrize("n", [400_003, 600_000])
+def test_levels_over_rows_in_topics(n, run, nq, k):
+    """Rows in the order of their topics (runs of similar rows, as documents are ingested): the levels'
+    rows are spread over the index, so the thresholds of a query on any topic are close, no buffer
+    overflows, and the index is read once."""
+    log("topics", n, run, nq, k)
+    d = 128
+    g = np.random.default_rng(n + run)
+    centres = g.integers(-7, 8, size=((n - 1) // run + 1, d)).astype(np.float32)
+    X = centres[np.arange(n) // run]
+    X += g.integers(-4, 5, size=X.shape, dtype=np.int8)
+    Q = centres[g.integers(0, len(centres), size=nq)]
+    dev = device()
+    idx = make_index(synth.to_storage(X, "bf16"), "bf16")
+    sc, ids = idx.search_dense(synth.to_storage(Q, "bf16").to(dev), k)
+    assert _overflowed(idx, nq, k) == 0
+    samp = np.r_[0:3, nq - 1]
+    ref_ids, ref_sc = od.topk_from_scores(Q[samp].astype(np.float64) @ X.astype(np.float64).T, k)
+    assert np.array_equal(ids.cpu().numpy()[samp], ref_ids)
+    assert np.array_equal(sc.cpu().numpy()[samp].astype(np.float64), ref_sc)
+    idx.close()
+
+
+@pytest.mark.parametrize("nq,k", [(70, 10), (600, 16), (70, 40)])
+def test_levels_overflow_where_no_level_looked(nq, k):
+    """The best rows, more than a buffer holds, all in 256-row blocks that only the last level has (its
+    predecessors take every fourth or eighth) and none of them the first level's: the buffers overflow, and
+    the repair finds the rows."""
+    log("hidden", nq, k)
+    n, d = 400_003, 128
+    g = np.random.default_rng(k)
+    X = g.integers(-2, 3, size=(n, d)).astype(np.float32)
+    X[:, :4] = 0
+    r = np.arange(n)
+    best = (r // 256 % 8 == 5) & (r % 256 < 60)  # 11,700 rows, their scores in no order of the rows
+    rows = n
+    while rows > 32_000:
+        rows = -(-rows // (8 if k <= 16 else 4))
+    for bm in (128, 256):  # the first level's tiles have one of these lengths
+        pitch = n // (rows // bm)
+        apart = (pitch // bm - 1) | 1  # odd
+        best[(np.arange(rows // bm)[:, None] * pitch + np.arange(bm) * apart).ravel()] = False
+    X[best, 0] = 64
+    X[best, 1] = g.integers(0, 128, size=int(best.sum()))
+    X[best, 2] = g.integers(0, 128, size=int(best.sum()))
+    Q = np.zeros((nq, d), np.float32)
+    Q[:, 0], Q[:, 1], Q[:, 2] = 64, 16, 1
+    Q[:, 4:8] = g.integers(-1, 2, size=(nq, 4))
+    dev = device()
+    idx = make_index(synth.to_storage(X, "bf16"), "bf16")
+    sc, ids = idx.search_dense(synth.to_storage(Q, "bf16").to(dev), k)
+    assert _overflowed(idx, nq, k) > 0
+    samp = np.r_[0:3, nq - 1]
+    ref_ids, ref_sc = od.topk_from_scores(Q[samp].astype(np.float64) @ X.astype(np.float64).T, k)
+    assert np.array_equal(ids.cpu().numpy()[samp], ref_ids)
+    assert np.array_equal(sc.cpu().numpy()[samp].astype(np.float64), ref_sc)
+    idx.close()
 
 
 @pytest.mark.parametrize("n", [3000, 32768, 140_000, 400_000])

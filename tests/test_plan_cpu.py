@@ -84,3 +84,32 @@ def test_workspace_bound_holds_and_stays_small(tmp_path):
     if (k_ws <= 16) CHECK(bound <= (nq_ws <= 64 ? 27u : 290u) << 20, "%zu bytes: d %d cap %lld nq %d k %d", bound, d, cap, nq_ws, k_ws)
   }
 """.replace("OPRAG_SCRATCH", "(32u << 20)"))
+
+
+def test_levels_are_spread_over_the_index(tmp_path):
+    """The threshold levels' tiles: each level's pitch a multiple of the next one's, the last level's
+    tiles the whole index, and the first level's rows spread over the index and within it."""
+    _run(tmp_path, r"""
+  for (int dtype : {kDtypeF32, kDtypeBF16})
+    for (int d : {128, 1024, 8192})
+      for (long long rows : {32769ll, 99999ll, 393217ll, 8450000ll, 500000000ll})
+        for (int nq : {1, 64, 65, 1000, 4096})
+          for (int k : {10, 17, 128}) {
+            const DensePlan p = plan_dense(dtype, d, rows, nq, k, kCus);
+            if (p.kind != DensePlan::kFilter) continue;
+            CHECK(p.n_levels >= 2 && (p.level_pitch[p.n_levels - 1] == 128 || p.level_pitch[p.n_levels - 1] == 256), "rows %lld", rows)
+            for (int l = 2; l < p.n_levels; ++l)
+              CHECK(p.level_pitch[l - 1] == (k <= 16 ? 8 : 4) * p.level_pitch[l], "rows %lld level %d", rows, l)
+            CHECK(p.level_rows[0] >= 3840 && p.level_rows[0] <= 32000, "rows %lld: %lld", rows, p.level_rows[0])
+            // tiles of 128 or 256 rows: the last one's last row, and how much of the index is spanned
+            int found = 0;
+            for (int bm : {128, 256}) {
+              const long long tiles = p.level_rows[0] / bm, last = (tiles - 1) * p.level_pitch[0] + (bm - 1) * (long long)p.row_pitch0;
+              if (p.level_pitch[0] != rows / tiles) continue;  // tiles of the other length
+              ++found;
+              CHECK(p.row_pitch0 >= 1 && last < rows, "rows %lld: the first level ends at %lld", rows, last)
+              CHECK((long long)bm * p.row_pitch0 * d * (dtype == kDtypeF32 ? 4 : 2) <= 1ll << 30, "rows %lld", rows)
+            }
+            CHECK(found > 0, "rows %lld: pitch %lld", rows, p.level_pitch[0])
+          }
+""")
