@@ -4,9 +4,10 @@
 //
 // Every search scores with the tiled matrix-core kernel of dense_tile.h and differs in what
 // the tiles hand on:
-//  - k <= 16: the largest score of every group of 4 to 64 (for long indexes more) rows; the k
+//  - up to 32,768 rows, and for k <= 16 few scores in all: every score; one workgroup per query selects
+//    from its score row;
+//  - k <= 16 otherwise: the largest score of every group of 4 to 64 (for long indexes more) rows; the k
 //    best groups of a query are found and their rows scored again (rescore_kernel);
-//  - k > 16, up to 32,768 rows: every score; one workgroup per query selects from its score row;
 //  - otherwise (k > 16, or more than 64 queries over a long index): threshold levels over growing
 //    shares of the rows.  The first level's group maxima give each query a lower bound of its k-th
 //    score; the next level collects only the rows that reach it, whose k-th score is the next
@@ -505,7 +506,14 @@ constexpr ShapeInfo kShapes[] = {{128, 16, 8, 1, 0.25, 0.9}, {128, 64, 4, 2, 0.5
                                  {256, 128, 4, 4, 0.84, 0.}, {128, 256, 2, 4, 0.85, 0.}, {256, 256, 2, 8, 1.0, 0.}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]), kNumShapes32 = 3;
 
-constexpr long long kDumpRows = 32768;        // k > 16: up to this many rows every score is kept
+constexpr long long kDumpRows = 32768;        // up to this many rows every score may be kept (the selection's most)
+// k <= 16: up to this many scores of a launch (times the row bytes over kDumpRow, where these are
+// more) are kept, 24 MiB at most.  Few scores are read back and selected from sooner than rows are scored
+// again, the more so the longer the rows: bf16, k = 10, group maxima against all scores in us:
+//   d 128:  64 queries x 10,000 rows 13.3 / 12.3, x 20,000 13.6 / 14.3; 1,024 x 1,000 17.8 / 16.6, x 4,000 18.5 / 23.0
+//   d 1024: 16 x 1,000 18.6 / 13.5, 64 x 32,768 22.7 / 22.2, 256 x 10,000 21.7 / 21.4, x 32,768 31.1 / 33.9
+//   d 4096: 256 x 20,000 69.3 / 60.3; fp32 d 1024: 16 x 1,000 33.4 / 23.4
+constexpr long long kDumpScores = 1ll << 20, kDumpMost = 6ll << 20, kDumpRow = 768;
 constexpr long long kMaximaRows = 393216;     // k <= 16, more than 64 queries: longer indexes filter
 // Up to this many groups (one pass of the rescoring workgroup) are searched directly, which saves a
 // dependent read (1.5 us of a call; batch 1 over 32,768 rows 21.3 -> 20.0 us), unless the batch is so
@@ -634,8 +642,14 @@ MaxGroups search_groups(int shape, int dtype, int d, long long rows, int nq, int
   }
 }
 
+long long dump_scores(int dtype, int d) {  // k <= 16
+  const long long row_bytes = (long long)d * elem_bytes(dtype);
+  return std::min(kDumpMost, kDumpScores * std::max(kDumpRow, row_bytes) / kDumpRow);
+}
+bool use_dump(int dtype, int d, long long rows, int nq, int k) {
+  return rows <= kDumpRows && (k > 16 || nq * rows <= dump_scores(dtype, d));
+}
 bool use_maxima(long long rows, int nq, int k) { return k <= 16 && (nq <= kMaximaQueries || rows <= kMaximaRows); }
-bool use_dump(long long rows, int k) { return k > 16 && rows <= kDumpRows; }
 
 // Candidate slots per query of the filter levels.  A level adds about (growth - 1) k of them (the first
 // one growth k).
@@ -650,8 +664,9 @@ size_t maxima_bytes(int nq, long long ld, long long cld) {
 size_t filter_body(int nq, int k) {
   return align_up256((size_t)nq * (size_t)filter_cap(k) * 8) + align_up256((size_t)nq * 4);
 }
-// k > 16, short index: room for a 64-bit key per row and query, more than the scores take.
-size_t dump_bytes(int nq, long long rows) {
+// Short index: the scores; k > 16: room for a 64-bit key per row and query, more than they take.
+size_t dump_bytes(int nq, long long rows, int k) {
+  if (k <= 16) return align_up256((size_t)nq * (size_t)((rows + 3) & ~3ll) * 4);
   return align_up256((size_t)nq * (size_t)std::max(1ll, rows) * 8) + align_up256((size_t)nq * 4) + 256;
 }
 
@@ -661,7 +676,9 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
   DensePlan p;
   p.n_cus = n_cus;
   p.shape = pick_shape(dtype, d, n_rows, nq, n_cus);
-  p.kind = use_maxima(n_rows, nq, k) ? DensePlan::kMaxima : (use_dump(n_rows, k) ? DensePlan::kDump : DensePlan::kFilter);
+  p.kind = use_dump(dtype, d, n_rows, nq, k) ? DensePlan::kDump
+           : use_maxima(n_rows, nq, k)       ? DensePlan::kMaxima
+                                             : DensePlan::kFilter;
   if (p.kind == DensePlan::kMaxima) {
     p.groups = search_groups(p.shape, dtype, d, n_rows, nq, k, n_cus);
     if (p.groups.count <= kOneLevel && nq <= 2 * n_cus) p.groups.coarse = p.groups.cld = 0;
@@ -717,7 +734,7 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
 
 size_t dense_workspace_bytes(const DensePlan& p, int dtype, int d, int nq, long long n_rows, int k) {
   if (p.kind == DensePlan::kMaxima) return maxima_bytes(nq, p.groups.ld, p.groups.cld);
-  if (p.kind == DensePlan::kDump) return dump_bytes(nq, n_rows);
+  if (p.kind == DensePlan::kDump) return dump_bytes(nq, n_rows, k);
   return filter_body(nq, k) + 256;
 }
 
@@ -752,8 +769,10 @@ size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k
     b = std::max(b, maxima(nq, std::min(capacity, kMaximaRows)));
     if (capacity > kMaximaRows) b = std::max(b, filter_body(nq, k1) + 256);
   }
+  // k <= 16, every score: of one row a query at least
+  b = std::max(b, align_up256((size_t)std::min(nq * std::min(capacity, kDumpRows), dump_scores(dtype, d)) * 4 + (size_t)nq * 16));
   if (k > 16) {
-    b = std::max(b, dump_bytes(nq, std::min(capacity, kDumpRows)));
+    b = std::max(b, dump_bytes(nq, std::min(capacity, kDumpRows), k));
     if (capacity > kDumpRows) b = std::max(b, filter_body(nq, k) + 256);
   }
   return b;

@@ -40,6 +40,26 @@ def test_tile_and_block_edges(dtype, d, n, nq, k):
     _check(*_ints(n + nq + k, n, d, nq), k, dtype)
 
 
+@pytest.mark.parametrize("dtype,d,n,nq,k", [
+    # k <= 16 at 2^20 scores (rows of up to 768 bytes): every score, and group maxima past it
+    ("bf16", 384, 1024, 1024, 10), ("bf16", 384, 1025, 1024, 10), ("f16", 128, 32_768, 32, 16),
+    ("f16", 128, 32_767, 33, 16), ("f32", 4, 16_131, 65, 5), ("f32", 4, 16_132, 65, 5),
+    # longer rows: as many times more scores, 6 * 2^20 at most; more than 32,768 rows: group maxima
+    ("bf16", 1024, 32_768, 64, 3), ("bf16", 1024, 21_845, 129, 3), ("f32", 3000, 6_000, 1040, 2),
+    ("f32", 3000, 6_050, 1040, 2), ("bf16", 128, 32_769, 1, 5), ("bf16", 128, 32_897, 16, 16)])
+def test_every_score_or_group_maxima(dtype, d, n, nq, k):
+    log("scores or maxima", dtype, d, n, nq, k)
+    _check(*_ints(n + nq + k, n, d, nq), k, dtype, samp=np.unique(np.r_[0:min(nq, 4), nq - 1]))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 384), ("f32", 100)])
+@pytest.mark.parametrize("n,nq,k", [(33_025, 1, 1), (33_151, 16, 5), (33_001, 17, 16), (16_511, 64, 3), (16_385, 65, 8),
+                                    (8_321, 128, 16), (8_193, 129, 5), (4_097, 257, 10), (1_153, 1000, 16)])
+def test_group_maxima_at_the_edges(dtype, d, n, nq, k):
+    log("maxima edges", dtype, d, n, nq, k)
+    _check(*_ints(n + nq, n, d, nq), k, dtype, samp=np.unique(np.r_[0:min(nq, 8), nq // 2, nq - 1]))
+
+
 @pytest.mark.parametrize("n,nq,k", [(400_001, 65, 1), (400_001, 130, 10), (393_217, 300, 16), (40_007, 66, 17),
                                     (300_003, 90, 128), (200_000, 5, 100)])
 def test_threshold_levels(n, nq, k):
