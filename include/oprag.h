@@ -151,7 +151,7 @@ oprag_status oprag_sparse_attach(oprag_index *idx, int32_t vocab, int64_t n_docs
  * OPRAG_OP_DENSE_FIRST, k_sparse the sparse k for OPRAG_OP_SPARSE and OPRAG_OP_HYBRID).  The
  * value does not depend on the current row count, so a workspace sized once stays valid as the
  * index grows, and a dense one serves smaller batches and smaller k as well.  With C the capacity:
- * a dense search with k <= 16 needs at most 27 MiB for up to 64 queries (about C bytes per query
+ * a dense search with k <= 16 needs at most 27 MiB for up to 64 queries (4 C bytes per query at most
  * before that), and at most 290 MiB for more; with k > 16 also 8 bytes per query and row
  * for up to 32,768 rows, or per query and candidate slot (64 k of them) beyond.
  */

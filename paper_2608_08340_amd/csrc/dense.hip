@@ -6,6 +6,8 @@
 // the tiles hand on:
 //  - up to 32,768 rows, and for k <= 16 few scores in all: every score; one workgroup per query selects
 //    from its score row;
+//  - up to 16 queries, k <= 16, over somewhat longer indexes: every score and their maxima over what a
+//    lane has of a chunk, through which one workgroup per query finds the best;
 //  - k <= 16 otherwise: the largest score of every group of 4 to 64 (for long indexes more) rows; the k
 //    best groups of a query are found and their rows scored again (rescore_kernel);
 //  - otherwise (k > 16, or more than 64 queries over a long index): threshold levels over growing
@@ -514,6 +516,12 @@ constexpr long long kDumpRows = 32768;        // up to this many rows every scor
 //   d 1024: 16 x 1,000 18.6 / 13.5, 64 x 32,768 22.7 / 22.2, 256 x 10,000 21.7 / 21.4, x 32,768 31.1 / 33.9
 //   d 4096: 256 x 20,000 69.3 / 60.3; fp32 d 1024: 16 x 1,000 33.4 / 23.4
 constexpr long long kDumpScores = 1ll << 20, kDumpMost = 6ll << 20, kDumpRow = 768;
+// Batches of up to 16 over longer indexes keep every score while a chunk's fit in LDS and they add a 32nd
+// to the index's bytes at most: reading scores back takes 4 us less than scoring rows again, and chunks
+// need not end with a tile.  bf16, k = 5, group maxima against all scores in us: 1 query over 65,536 x 1,024
+// 30.5 / 26.4, 150,000 57.0 / 53.0, 300,000 121.5 / 116.3, 1 M 353 / 347 (k = 10); 16 queries 30.7 / 27.3 and
+// 58.7 / 58.5; f16 168,344 x 512, 4 queries 37.2 / 33.9; 100,000 x 256, 4 queries 20.3 / 17.6.
+constexpr long long kScoresShare = 4 * 32;
 constexpr long long kMaximaRows = 393216;     // k <= 16, more than 64 queries: longer indexes filter
 // Up to this many groups (one pass of the rescoring workgroup) are searched directly, which saves a
 // dependent read (1.5 us of a call; batch 1 over 32,768 rows 21.3 -> 20.0 us), unless the batch is so
@@ -649,6 +657,10 @@ long long dump_scores(int dtype, int d) {  // k <= 16
 bool use_dump(int dtype, int d, long long rows, int nq, int k) {
   return rows <= kDumpRows && (k > 16 || nq * rows <= dump_scores(dtype, d));
 }
+bool use_scores(int dtype, int d, long long rows, int nq, int k, int n_cus) {
+  return k <= 16 && rows > kDumpRows && nq <= 16 && kScoresShare * nq <= (long long)d * elem_bytes(dtype) &&
+         nq * tile_grid(0, dtype, d, rows, nq, n_cus).most <= kHeldTiles;
+}
 bool use_maxima(long long rows, int nq, int k) { return k <= 16 && (nq <= kMaximaQueries || rows <= kMaximaRows); }
 
 // Candidate slots per query of the filter levels.  A level adds about (growth - 1) k of them (the first
@@ -679,7 +691,12 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
   p.kind = use_dump(dtype, d, n_rows, nq, k) ? DensePlan::kDump
            : use_maxima(n_rows, nq, k)       ? DensePlan::kMaxima
                                              : DensePlan::kFilter;
-  if (p.kind == DensePlan::kMaxima) {
+  if (use_scores(dtype, d, n_rows, nq, k, n_cus)) {
+    p.kind = DensePlan::kScores;
+    p.shape = 0;
+    p.ld = (n_rows + 3) & ~3ll;
+    p.groups = max_groups(p.shape, dtype, d, n_rows, nq, n_cus, 4);
+  } else if (p.kind == DensePlan::kMaxima) {
     p.groups = search_groups(p.shape, dtype, d, n_rows, nq, k, n_cus);
     if (p.groups.count <= kOneLevel && nq <= 2 * n_cus) p.groups.coarse = p.groups.cld = 0;
   } else if (p.kind == DensePlan::kDump) {
@@ -734,6 +751,7 @@ DensePlan plan_dense(int dtype, int d, long long n_rows, int nq, int k, int n_cu
 
 size_t dense_workspace_bytes(const DensePlan& p, int dtype, int d, int nq, long long n_rows, int k) {
   if (p.kind == DensePlan::kMaxima) return maxima_bytes(nq, p.groups.ld, p.groups.cld);
+  if (p.kind == DensePlan::kScores) return maxima_bytes(nq, p.ld, p.groups.cld);
   if (p.kind == DensePlan::kDump) return dump_bytes(nq, n_rows, k);
   return filter_body(nq, k) + 256;
 }
@@ -761,7 +779,9 @@ size_t dense_workspace_bound(int dtype, int d, long long capacity, int nq, int k
                                      : (size_t)16 * std::min(queries, 512) * (size_t)n_cus +
                                            (size_t)queries * 16 * (size_t)by_len);
     const size_t most = small ? std::max(kMaximaBytes, coarse) : kBatchMaximaBytes;  // (small: a unit per chunk at least)
-    const size_t fine = std::min((size_t)queries * (size_t)((groups + 3) & ~3ll) * 4, most);
+    size_t fine = std::min((size_t)queries * (size_t)((groups + 3) & ~3ll) * 4, most);
+    // kScores: as many as the CUs hold, in as many chunks
+    fine = std::max(fine, (size_t)std::min(std::min(queries, 16) * rows, (long long)kHeldTiles * 128 * n_cus) * 4 + 256);
     return align_up256(fine) + align_up256(coarse + (size_t)queries * 16);
   };
   size_t b = maxima(std::min(nq, kMaximaQueries), capacity);
@@ -812,8 +832,9 @@ hipError_t launch_maxima(int dtype, int shape, int mode, const MaxGroups& m, con
   return launch_tiles(dtype, shape, mode, arg, set, n_cus, s, ev0, ev1);
 }
 
+// scores_ld > 0: from every score (that far apart) and the coarse maxima.
 hipError_t launch_rescore(int dtype, int shape, const MaxGroups& m, const DenseArgs& a, int n_cus, const int* gate,
-                          hipStream_t s) {
+                          hipStream_t s, long long scores_ld = 0) {
   const ShapeInfo& sh = kShapes[shape];
   const TileGrid g = tile_grid(shape, dtype, a.d, a.n_rows, a.nq, n_cus);
   RescoreArgs r;
@@ -830,6 +851,13 @@ hipError_t launch_rescore(int dtype, int shape, const MaxGroups& m, const DenseA
   r.coarse_ld = m.cld;
   r.n_coarse = m.coarse;
   r.two = m.count > 0 && m.coarse > 0;
+  if (scores_ld > 0) {
+    r.scores = 1;
+    r.fine_ld = scores_ld;
+    r.n_fine = (int)a.n_rows;
+    r.coarse = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.partial) +
+                                              align_up256((size_t)a.nq * (size_t)scores_ld * 4));
+  }
   r.tile_rows = sh.bm;
   r.n_chunks = g.n_chunks;
   r.least = (int)(g.tiles / g.n_chunks);
@@ -884,6 +912,18 @@ hipError_t launch_dense(const DensePlan& p, int dtype, const DenseArgs& a, hipSt
                                        all_tiles(kShapes[p.shape], a.n_rows), p.n_cus, nullptr, s, ev0, ev1);
     if (e != hipSuccess) return e;
     return launch_rescore(dtype, p.shape, p.groups, a, p.n_cus, nullptr, s);
+  }
+  if (p.kind == DensePlan::kScores) {
+    DenseArgs arg = a;
+    arg.dump = reinterpret_cast<float*>(a.partial);
+    arg.dump_ld = p.ld;
+    arg.cmx = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.partial) +
+                                       align_up256((size_t)a.nq * (size_t)p.ld * 4));
+    arg.cmx_ld = p.groups.cld;
+    const hipError_t e = launch_tiles(dtype, p.shape, kTileScores, arg, all_tiles(kShapes[p.shape], a.n_rows), p.n_cus, s,
+                                      ev0, ev1);
+    if (e != hipSuccess) return e;
+    return launch_rescore(dtype, p.shape, p.groups, a, p.n_cus, nullptr, s, p.ld);
   }
   if (p.kind == DensePlan::kDump) {
     DenseArgs arg = a;

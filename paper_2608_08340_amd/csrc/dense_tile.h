@@ -21,6 +21,7 @@
 //  - MAX: the largest score of every group of rows, for a search that finds the k best groups and
 //    scores their rows again (rescore_kernel): no list is kept and nothing is exchanged between
 //    waves, so the epilogue is a few dozen instructions;
+//  - SCORES: every score and the largest of a lane's over its chunk, for small batches;
 //  - FILT: the scores that reach their query's threshold become candidates;
 //  - DUMP: every score;
 #pragma once
@@ -108,6 +109,11 @@ struct TileQueue {
   static_assert(BN <= 256 && kChunkRowBits + 8 <= 32, "row offset and query slot share 32 bits");
 };
 
+// SCORES: the first row of a chunk.
+__device__ __forceinline__ long long scores_chunk_row(long long chunk, long long n_rows, int n_chunks) {
+  return chunk * ((n_rows + 15) / 16) / n_chunks * 16;
+}
+
 template <int DT, int BM, int BN, int MODE>
 __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   if (a.gate != nullptr && *a.gate == 0) return;  // a repair launch with nothing to repair
@@ -116,7 +122,8 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   using S = TileShape<BM, BN>;
   constexpr bool UNITS = MODE == kTileUnits, SAMPLE = MODE == kTileSample;
   constexpr bool MAX = MODE == kTileMax || UNITS || SAMPLE;
-  constexpr int MP = S::MP, MS = S::MS, NP = S::NP, NS = S::NS, NBUF = S::NBUF;
+  constexpr int MP = S::MP, MS = S::MS, NP = S::NP, NS = S::NS;
+  constexpr int NBUF = MODE == kTileScores ? S::NBUF - 1 : S::NBUF;  // (the scores take the place of a stage)
   constexpr int MT = MP * MS, NT = NP * NS;          // subtiles per wave
   constexpr int AI = BM / MP / 64;            // load instructions per wave and part: rows,
   constexpr int BI = S::BR / NP / 64;                // queries
@@ -128,7 +135,10 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   static_assert(MP == 1 || (NP == 2 && NBUF == 2), "schedules");
   static_assert(AI >= 1 && BI >= 1 && BUF <= 65536, "parts and immediates");
   using Q = TileQueue<BM, BN>;
-  constexpr int SMEM = MODE == kTileFilt ? Q::kLds + Q::CAP * 8 + BN * 12 + 64 : Q::kLds;
+  constexpr int SMEM = MODE == kTileFilt     ? Q::kLds + Q::CAP * 8 + BN * 12 + 64
+                       : MODE == kTileScores ? NBUF * BUF + kHeldTiles * BM * 4
+                                             : Q::kLds;
+  static_assert(SMEM <= 163840, "LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   u64* queue = reinterpret_cast<u64*>(smem + Q::kLds);
   int* qhist = reinterpret_cast<int*>(smem + Q::kLds + (MODE == kTileFilt ? Q::CAP * 8 : 0));  // [BN]
@@ -148,15 +158,22 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
   const int nkt = max(2, (rowb + 127) / 128);        // 128-byte stages per tile
   // The chunk has tiles j0 .. j0 + n_tiles - 1 of the launch's (DenseArgs).
   constexpr bool SKIPS = MODE == kTileFilt;
-  const int j0 = (int)(chunk * a.tiles / a.n_chunks);
-  const int n_tiles = a.n_rows > 0 ? (int)((chunk + 1) * a.tiles / a.n_chunks) - j0 : 0;
+  constexpr bool SCORES = MODE == kTileScores;
+  int j0 = (int)(chunk * a.tiles / a.n_chunks);
+  int n_tiles = a.n_rows > 0 ? (int)((chunk + 1) * a.tiles / a.n_chunks) - j0 : 0;
   const int tile_pitch = SKIPS || SAMPLE ? a.tile_pitch : BM, row_pitch = SAMPLE ? a.row_pitch : 1;
   auto tile_row = [&](unsigned j) __attribute__((always_inline)) {  // the first row of tile j
     if constexpr (SKIPS) j += __umulhi(j, a.skip_recip) + (a.skip > 0 ? 1u : 0u);
     return (unsigned)tile_pitch * j;
   };
-  const long long row_begin = tile_row(j0);
-  const long long row_end = min((long long)tile_row(j0 + max(n_tiles, 1) - 1) + BM * row_pitch, a.n_rows);
+  long long row_begin = tile_row(j0);
+  long long row_end = min((long long)tile_row(j0 + max(n_tiles, 1) - 1) + BM * row_pitch, a.n_rows);
+  if constexpr (SCORES) {  // chunks of as equal numbers of rows as 16-row steps allow
+    j0 = 0;
+    row_begin = scores_chunk_row(chunk, a.n_rows, a.n_chunks);
+    row_end = min(scores_chunk_row(chunk + 1, a.n_rows, a.n_chunks), a.n_rows);
+    n_tiles = (int)((row_end - row_begin + BM - 1) / BM);
+  }
   // Row of the index, from the tile's first, at position r of the tile.  SAMPLE: similar rows, which are
   // often neighbours, go to groups of their own (a lane's four positions are a quarter of the tile apart, those
   // of its next subtile an eighth).  The bits of r count separately.
@@ -217,7 +234,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
     // Byte offset of the chunk's tile i.  (Past the chunk it may wrap, of a single tile's chunk and a very
     // long pitch: such loads land inside the chunk again and are never used.)
     auto tile_ofs = [&](int i) __attribute__((always_inline)) {
-      return (tile_row((unsigned)(j0 + i)) - (unsigned)row_begin) * (unsigned)rowb;
+      return (tile_row((unsigned)(j0 + i)) - tile_row((unsigned)j0)) * (unsigned)rowb;
     };
     // Cursors (byte offsets of the next stage to load): x for the parts loaded LA stages ahead,
     // y (MP 2) for the second parts, one stage ahead.  Past the chunk nothing is read.  Each goes on to its
@@ -434,6 +451,29 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
           }
           if (a.cmx != nullptr && PA == MP - 1 && t == n_tiles - 1 && q < a.nq)
             a.cmx[(long long)q * a.cmx_ld + chunk * (S::WM * 4) + (wm * 4 + (lane >> 4))] = x;
+        } else if constexpr (SCORES) {
+          // The scores wait in LDS (each lane's for itself) until the chunk's end: a store has the counted waits
+          // after it wait for its reply.  (In registers the unrolled code cost 1.5 us with 16 tiles, 4 with 32.)
+          static_assert(MT == 1 && NT == 1);
+          f32x4 x = acc[0][0];
+          if (!full) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = r < lim ? x[r] : __builtin_nanf("");
+          }
+          dmx[0] = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(t == 0 ? __builtin_nanf("") : dmx[0], x[0]),
+                                                   __builtin_fmaxf(x[1], x[2])), x[3]);
+          if (q < a.nq) {
+            f32x4* held = reinterpret_cast<f32x4*>(smem + NBUF * BUF) + ((lane & 15) * BM + row0) / 4;
+            const int step = a.nq * BM / 4;
+            held[t * step] = x;
+            if (t == n_tiles - 1) {  // workgroup-uniform
+              float* dst = a.dump + (long long)q * a.dump_ld + row_begin + row0;
+#pragma unroll 2
+              for (int u = 0; u < n_tiles; ++u)
+                if (u * BM + row0 < rows) *reinterpret_cast<f32x4*>(dst + u * BM) = held[u * step];
+              a.cmx[(long long)q * a.cmx_ld + chunk * (S::WM * 4) + (wm * 4 + (lane >> 4))] = dmx[0];
+            }
+          }
         } else if constexpr (MODE == kTileDump) {
           if (q < a.nq) {
             float* dst = a.dump + (long long)q * a.dump_ld + row_begin + trow + row0;
@@ -565,7 +605,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
       } else {
         for (int k = 0; k < nkt; ++k) stage(I0);
       }
-      trow = (int)(tile_row((unsigned)(j0 + t)) - (unsigned)row_begin);
+      trow = (int)(tile_row((unsigned)(j0 + t)) - tile_row((unsigned)j0));
       full = trow + BM <= rows;
       lim = min(BM, rows - trow) - row0;
       if constexpr (MODE == kTileFilt) {
@@ -701,8 +741,9 @@ constexpr int kReCand = 64;                              // groups ranked by a w
 constexpr int kReList = 256;                             // groups scored: k + the groups of one tile
 constexpr int kReRows = 1024;                            // rows ranked together
 
-template <int DT, bool UNITS>
+template <int DT, int KIND>
 __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
+  constexpr bool UNITS = KIND == kTileUnits, SCORES = KIND == kTileScores;
   if (a.gate != nullptr && *a.gate == 0) return;
   using M = Mfma<DT>;
   using V = typename M::V;
@@ -717,8 +758,8 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
   __shared__ int s_n, s_nh, s_nl, s_k[2];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const long long q = blockIdx.x;
-  const bool two = a.two != 0;           // launch-uniform: groups searched through the coarse maxima
-  const bool by_chunk = a.fine == nullptr;  // the coarse maxima are the groups
+  const bool two = SCORES || a.two != 0;  // launch-uniform: groups searched through the coarse maxima
+  const bool by_chunk = !SCORES && a.fine == nullptr;  // the coarse maxima are the groups
   const int k = a.k;
   const int rowb = a.d * (DT == kDtypeF32 ? 4 : 2);
   const int np = rowb / 16;  // 16-byte pieces of a row
@@ -759,7 +800,7 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
     s_nl = 0;
     s_k[0] = s_k[1] = 0;
   }
-  {
+  if constexpr (!SCORES) {
     const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(a.Q) + q * rowb);
     for (int i = t; i < np; i += NT) reinterpret_cast<u32x4*>(qrow)[i] = src[i];
   }
@@ -826,7 +867,19 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
   auto first_tile = [&](int chunk) { return chunk * a.least + (int)((unsigned)(chunk * a.spare) / (unsigned)a.n_chunks); };
   if (two) {
     const int nh = s_nh, per = (UNITS ? a.upc : a.most) << gl_sh;  // groups of a lane over its chunk
-    if (nh <= kReCand)
+    if constexpr (SCORES) {
+      if (nh <= kReCand)
+        for (int p = t; p < nh * per; p += NT) {
+          const int c = clist[p / per], u = p % per, chunk = c >> lanes_sh, l = c & ((1 << lanes_sh) - 1);
+          const long long row = scores_chunk_row(chunk, a.n_rows, a.n_chunks) + u * a.tile_rows + (l >> 2) * 16 + (l & 3) * 4;
+          if (row < min(scores_chunk_row(chunk + 1, a.n_rows, a.n_chunks), a.n_rows)) {
+            const float4 x = *reinterpret_cast<const float4*>(groups + row);  // (NaN past the last row)
+            const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) offer(v[e], (int)row + e);
+          }
+        }
+    } else if (nh <= kReCand)
       for (int p = t; p < nh * per; p += NT) {
         const int c = clist[p / per], u = p % per, chunk = c >> lanes_sh, l = c & ((1 << lanes_sh) - 1);
         const int unit0 = UNITS ? chunk * a.upc : first_tile(chunk);  // tiles or units
@@ -851,6 +904,17 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
     int r = 0;
 #pragma unroll 4
     for (int o = 0; o < nc; ++o) r += cand[o] > me ? 1 : 0;
+    if constexpr (SCORES) {
+      if (w == 0 && lane < nc && r < k) {
+        a.out_ids[q * k + r] = (long long)comp_row(me);
+        a.out_scores[q * k + r] = comp_score(me);
+      }
+      for (int r2 = need + t; r2 < k; r2 += NT) {
+        a.out_ids[q * k + r2] = -1ll;
+        a.out_scores[q * k + r2] = kNegInf;
+      }
+      return;
+    }
     const u64 is = __ballot(lane < nc && r == need - 1);
     if (is != 0ull) {
       const u64 star = readlane64(me, __builtin_ctzll(is));
@@ -883,9 +947,16 @@ __global__ __launch_bounds__(kReThreads, 4) void rescore_kernel(RescoreArgs a) {
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < NW; ++u) x = umax64(x, red[u]);
+      if constexpr (SCORES) {
+        if (t == 0) {
+          a.out_ids[q * k + r] = x != 0ull ? (long long)comp_row(x) : -1ll;
+          a.out_scores[q * k + r] = x != 0ull ? comp_score(x) : kNegInf;
+        }
+      }
       if (x != 0ull) last = x;  // fewer than k groups: the last one
       __syncthreads();
     }
+    if constexpr (SCORES) return;
     const u64 star = last;
     for (int i = t; i < n4; i += NT) {
       const float4 y = word_of(all, n, i);
@@ -1056,6 +1127,7 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
     OPRAG_TILE(4, 128, 256)
     OPRAG_TILE(5, 256, 256)
   }
+  if (mode == kTileScores) fn = shape == 0 ? dense_tile_kernel<DT, 128, 16, kTileScores> : nullptr;
   if (mode == kTileUnits)
     fn = shape == 0   ? dense_tile_kernel<DT, 128, 16, kTileUnits>
          : shape == 1 ? dense_tile_kernel<DT, 128, 64, kTileUnits>
@@ -1073,10 +1145,12 @@ hipError_t tile_launch(int shape, int mode, long long grid, DenseArgs& arg, hipS
 template <int DT>
 hipError_t rescore_launch(const RescoreArgs& a, int nq, hipStream_t s) {
   const size_t lds = (size_t)a.d * (DT == kDtypeF32 ? 4 : 2);
-  if (a.unit_sh > 0)
-    hipLaunchKernelGGL((rescore_kernel<DT, true>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
+  if (a.scores)
+    hipLaunchKernelGGL((rescore_kernel<DT, kTileScores>), dim3((unsigned)nq), dim3(kReThreads), 0, s, a);
+  else if (a.unit_sh > 0)
+    hipLaunchKernelGGL((rescore_kernel<DT, kTileUnits>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
   else
-    hipLaunchKernelGGL((rescore_kernel<DT, false>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
+    hipLaunchKernelGGL((rescore_kernel<DT, kTileMax>), dim3((unsigned)nq), dim3(kReThreads), lds, s, a);
   return hipGetLastError();
 }
 

@@ -12,11 +12,12 @@ namespace oprag {
 constexpr int kMaxK = 128;                 // largest k any list may ask for
 constexpr int kMaxQPerLaunch = 4096;       // queries per dense launch (the host splits larger batches evenly)
 constexpr int kChunkRowBits = 24;          // rows of a dense chunk: a queued hit keeps its offset in so many bits
+constexpr int kHeldTiles = 80;             // kTileScores: most tiles of a chunk times queries (their scores fit LDS)
 constexpr int kDtypeF32 = 0, kDtypeBF16 = 1, kDtypeF16 = 2;
 
 // Modes of the tiled scoring kernel (kTileUnits: kTileMax with groups that span tiles; kTileSample: of
-// rows spread over the index).
-enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2, kTileUnits = 3, kTileSample = 4 };
+// rows spread over the index; kTileScores: every score, and the coarse maxima).
+enum TileMode { kTileMax = 0, kTileFilt = 1, kTileDump = 2, kTileUnits = 3, kTileSample = 4, kTileScores = 5 };
 
 struct DenseArgs {
   const void* X;                // slab rows [n_rows x d]
@@ -95,6 +96,7 @@ struct RescoreArgs {
   int least = 0, spare = 0;      // tiles / n_chunks, tiles % n_chunks
   int gpt_sh = 0, lanes_sh = 0, gl_sh = 0, gs_sh = 0, mt_sh = 0;
   int unit_sh = 0, upc = 0;
+  int scores = 0;                // fine holds every score ([nq x fine_ld] by row), of kTileScores
   float* out_scores = nullptr;
   long long* out_ids = nullptr;
   const int* gate = nullptr;
@@ -108,13 +110,13 @@ template <int DT>
 hipError_t rescore_launch(const RescoreArgs& a, int nq, hipStream_t s);
 
 // How a search of one launch runs (dense.hip): group maxima and rescoring, every score and a
-// selection, or threshold levels.
+// selection (kScores: through coarse maxima), or threshold levels.
 struct DensePlan {
-  enum Kind { kMaxima, kDump, kFilter };
+  enum Kind { kMaxima, kDump, kScores, kFilter };
   Kind kind = kMaxima;
   int n_cus = 0;                // compute units of the device the plan is for
   int shape = 0;                // tile shape over all rows
-  long long ld = 0;             // kDump: row stride of the scores
+  long long ld = 0;             // kDump, kScores: row stride of the scores
   MaxGroups groups;             // kMaxima, and kFilter's first level
   // kFilter
   int shape0 = 0;               // tile shape of the first level

@@ -52,6 +52,45 @@ def test_every_score_or_group_maxima(dtype, d, n, nq, k):
     _check(*_ints(n + nq + k, n, d, nq), k, dtype, samp=np.unique(np.r_[0:min(nq, 4), nq - 1]))
 
 
+@pytest.mark.parametrize("dtype,d,n,nq,k", [
+    # every score and the lanes' maxima: 128 bytes of a row per query, and one query more (group maxima)
+    ("bf16", 128, 32_769, 2, 16), ("bf16", 128, 33_003, 3, 5), ("f32", 100, 41_001, 3, 10), ("f32", 100, 41_001, 4, 10),
+    ("bf16", 1024, 32_785, 16, 16), ("f16", 256, 65_535, 4, 1),
+    # tiles of a chunk times queries 80 and past it (group maxima), on 256 CUs
+    ("bf16", 256, 655_360, 4, 5), ("bf16", 256, 655_361, 4, 5), ("f32", 32, 2_621_440, 1, 16),
+    ("f32", 32, 2_621_441, 1, 16), ("bf16", 1024, 65_536, 16, 3), ("bf16", 256, 163_001, 3, 1)])
+@pytest.mark.parametrize("spread", [1, 2])
+def test_few_queries_over_long_indexes(dtype, d, n, nq, k, spread):
+    log("few queries", dtype, d, n, nq, k, spread)
+    _check(*_ints(n + nq, n, d, nq, spread=spread), k, dtype)
+
+
+@pytest.mark.parametrize("n,nq", [(40_000, 1), (200_003, 2)])
+@pytest.mark.parametrize("case", ["ties", "nan", "few"])
+def test_few_queries_with_ties_and_nan(n, nq, case):
+    """More rows at the threshold than are ranked at once; NaN rows; fewer than k rows with a number."""
+    log("few queries", case, n, nq)
+    X, Q = _ints(n, n, 128, nq, spread=3)
+    if case == "ties":
+        X[n // 3:] = 0
+        Q[0] = 0
+    else:
+        bad = np.random.default_rng(n).permutation(n)[:n // 2 if case == "nan" else n - 3]
+        X[bad, 0] = np.nan
+        Q[:, 0] = 1
+    dev = device()
+    idx = make_index(synth.to_storage(X, "bf16"), "bf16")
+    sc, ids = idx.search_dense(synth.to_storage(Q, "bf16").to(dev), 16)
+    sc, ids = sc.cpu().numpy().astype(np.float64), ids.cpu().numpy()
+    S = Q.astype(np.float64) @ X.astype(np.float64).T
+    for i in range(nq):
+        rows = np.flatnonzero(~np.isnan(S[i]))
+        best = rows[np.lexsort((rows, -S[i][rows]))][:16]
+        assert np.array_equal(ids[i][:len(best)], best) and np.array_equal(sc[i][:len(best)], S[i][best])
+        assert np.all(ids[i][len(best):] == -1) and np.all(sc[i][len(best):] == -np.inf)
+    idx.close()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 384), ("f32", 100)])
 @pytest.mark.parametrize("n,nq,k", [(33_025, 1, 1), (33_151, 16, 5), (33_001, 17, 16), (16_511, 64, 3), (16_385, 65, 8),
                                     (8_321, 128, 16), (8_193, 129, 5), (4_097, 257, 10), (1_153, 1000, 16)])
