@@ -490,7 +490,10 @@ __global__ void clear_ints_kernel(int* p, long long n, const int* gate) {
 // ------------------------------------------------------------------------------------
 // Planning.
 // ------------------------------------------------------------------------------------
-constexpr int kMaximaQueries = 64;  // k <= 16: up to this many queries group maxima at any length
+// k <= 16: up to this many queries group maxima at any length.  Their memory fits the search without a workspace
+// then, and no data makes them slow; rows in random order would be filtered as fast: bf16, 64 queries, group
+// maxima against levels 179 / 186 us over 393,216 x 1,024, 263 / 252 over 600,000, 408 / 388 over 1 M.
+constexpr int kMaximaQueries = 64;
 // Most bytes of a launch's group maxima: of up to 64 queries (so that any index length fits the fixed
 // array of the search without a workspace), and of larger batches.
 constexpr size_t kMaximaBytes = 24ull << 20, kBatchMaximaBytes = 256ull << 20;
@@ -500,6 +503,10 @@ constexpr size_t kMaximaBytes = 24ull << 20, kBatchMaximaBytes = 256ull << 20;
 // smaller ones): fewer MFMAs per byte read from LDS and per barrier.  The 16-query shape serves
 // batches of up to 16, where the rows' bytes bound every shape and the smallest epilogue is best.
 // fp32: the MFMAs themselves bound every shape, so padded work decides.
+// Of each shape forced in turn, 80 to 3,000 queries, the choice is within 3 % of the fastest at 384 to 4,096
+// dimensions (32,768 x 1,024, 99,991 x 768, 150,000 x 384, 20,000 x 4,096); at 128, where the epilogue counts
+// as much as the two stages, 256 x 256 tiles are up to 25 % slower than 128 x 256 ones (393,000 rows, 256 queries 89 /
+// 66 us).
 struct ShapeInfo {
   int bm, bn, wm, mt;  // tile rows and queries, waves along the rows, subtiles per wave
   double eff, eff32;
@@ -522,7 +529,11 @@ constexpr long long kDumpScores = 1ll << 20, kDumpMost = 6ll << 20, kDumpRow = 7
 // 30.5 / 26.4, 150,000 57.0 / 53.0, 300,000 121.5 / 116.3, 1 M 353 / 347 (k = 10); 16 queries 30.7 / 27.3 and
 // 58.7 / 58.5; f16 168,344 x 512, 4 queries 37.2 / 33.9; 100,000 x 256, 4 queries 20.3 / 17.6.
 constexpr long long kScoresShare = 4 * 32;
-constexpr long long kMaximaRows = 393216;     // k <= 16, more than 64 queries: longer indexes filter
+// k <= 16, more than 64 queries: longer indexes filter.  The line is where 512 queries gain from
+// neither; fewer queries would cross at some 800,000 rows, more at 300,000.  bf16 x 1,024, group maxima against
+// levels in us: 65 queries over 393,216 rows 167 / 195, 600,000 256 / 276, 1 M 410 / 397; 512 queries 377 / 407,
+// 565 / 585, 933 / 890; 2,048 queries over 200,000 rows 735 / 811, 393,216 1,462 / 1,345, 600,000 2,218 / 2,001.
+constexpr long long kMaximaRows = 393216;
 // Up to this many groups (one pass of the rescoring workgroup) are searched directly, which saves a
 // dependent read (1.5 us of a call; batch 1 over 32,768 rows 21.3 -> 20.0 us), unless the batch is so
 // large that the maxima's bytes count (batch 1,024: 15.6 us, 14.5 through the coarse ones).

@@ -1,4 +1,4 @@
-// Dense scoring of bf16 / fp16 query batches as a tiled matrix product on the matrix cores
+// Dense scoring of bf16, fp16 and fp32 query batches as a tiled matrix product on the matrix cores
 // (Section 4.4: vectorised scoring over the embedding matrix), with the selection's first step
 // in the epilogue of every tile.
 //
@@ -85,7 +85,8 @@ __device__ __forceinline__ rsrc_t tile_rsrc(const void* base, long long bytes) {
 
 // 64 lanes x 16 bytes from a buffer resource to LDS [lds, lds + 1024), lane after lane; past the
 // resource's end nothing is read.  (Written out because the compiler would drain every load
-// before any LDS read; the load has no destination register.)
+// before any LDS read; the load has no destination register.  m0 is no clobber: the compiler reserves it,
+// writes it before each use of its own, and refuses to preserve it.)
 __device__ __forceinline__ void lds_load16(rsrc_t r, int voff, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r)
                : "memory");
@@ -716,7 +717,7 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
-// The k best rows of each query from the maxima of MAX mode, one workgroup per query.  Up to 8,192
+// The k best rows of each query from the maxima of MAX mode (or the scores of SCORES), one workgroup per query.  Up to 8,192
 // groups are searched directly; of more, every lane's maximum over its chunk (the coarse maxima, at
 // most some 8,192 a query) bounds the k-th score from below and says where the groups that reach
 // that bound lie, and only those lanes' groups are read.  With the groups ordered by (maximum desc,
@@ -725,7 +726,9 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
 // hold a row at least as good).  These groups' rows, k of them and the ties in c's tile, are scored
 // again with the same matrix instructions in the same order as in the tile kernel, so the scores
 // have the same bits, and ranked exactly.  Without groups (fine == nullptr) the coarse maxima are the
-// groups, over all of a lane's rows.
+// groups, over all of a lane's rows.  With every score at hand (SCORES) the coarse maxima's lanes that reach
+// the bound are read back, four rows a word, and the scores that reach it are ranked: 4 us less than with rows
+// scored again.
 //
 // A launch of a few workgroups is bound by latency.  One query over 32,768 rows of 1,024 bf16 takes
 // 7.0 us from start to end: 1.4 the maxima (the first reads), 0.7 tau, 1.1 the groups' order, 2.6 the

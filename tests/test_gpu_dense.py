@@ -54,9 +54,9 @@ def c2():
 
 @pytest.mark.parametrize("nq", [1, 16, 65, 128, 256, 384, 768, 1024])
 def test_32k_x_1024_bf16_top5(c2, nq):
-    """32,768 x 1,024 bf16 mixture rows; query batches 1, 16, 256, 384, 768, 1,024; exact
-    top-5.  384 and 768 queries (three and six query blocks) get grids of fewer workgroups
-    than CUs, with two and four tiles per chunk."""
+    """32,768 x 1,024 bf16 mixture rows; query batches 1, 16, 65, 128, 256, 384, 768, 1,024; exact
+    top-5.  384 and 768 queries (several query blocks) get grids of fewer workgroups than CUs, with
+    several tiles per chunk."""
     log("32k bf16 nq", nq)
     q = c2.queries[:nq].contiguous()
     _, sc, ids = _run(c2.rows, q, 5, "bf16")
@@ -67,8 +67,7 @@ def test_32k_x_1024_bf16_top5(c2, nq):
 
 @pytest.mark.parametrize("k", [8, 16])
 def test_32k_x_1024_bf16_top8_top16_batch512(c2, k):
-    """32,768 x 1,024 bf16, 512 queries, k = 8 and 16: the 128-query kernels with the running
-    threshold on every tile after a chunk's first (two tiles per chunk at this batch)."""
+    """32,768 x 1,024 bf16, 512 queries, k = 8 and 16: group maxima of several tiles a chunk."""
     log("32k bf16 nq 512 k", k)
     q = c2.queries[:512].contiguous()
     _, sc, ids = _run(c2.rows, q, k, "bf16")
@@ -79,9 +78,8 @@ def test_32k_x_1024_bf16_top8_top16_batch512(c2, k):
 
 @pytest.mark.parametrize("nq,k", [(1, 10), (1, 16), (16, 16), (64, 10), (64, 16), (100, 8), (100, 16), (128, 10)])
 def test_32k_x_1024_bf16_small_batch_top10_top16(c2, nq, k):
-    """32,768 x 1,024 bf16 at small batches with k = 10 and 16: 128 to 256 chunk lists of k
-    entries per query, merged from one load batch of 64 composites per lane (sorted lists whose
-    length divides 64, the case where lanes must not all see the same list position)."""
+    """32,768 x 1,024 bf16 at small batches with k = 8 to 16: every score and a selection up to 64
+    queries, group maxima above."""
     log("32k bf16 nq", nq, "k", k)
     q = c2.queries[:nq].contiguous()
     _, sc, ids = _run(c2.rows, q, k, "bf16")
@@ -92,9 +90,7 @@ def test_32k_x_1024_bf16_small_batch_top10_top16(c2, nq, k):
 
 @pytest.mark.parametrize("nq,k", [(1, 16), (16, 10), (50, 16)])
 def test_long_list_merge_with_a_short_last_chunk(nq, k):
-    """19,973 rows (156 full 128-row chunks and one of 5 rows, so one list holds fewer than k
-    entries and is padded) at small batches: with k = 16, 2,512 composites per query, the
-    workgroup-per-query merge; with k = 10, the one-wave merge of 1,570."""
+    """19,973 rows: 156 full 128-row tiles and one of 5 rows, at small batches."""
     log("long list merge", nq, k)
     device()
     w = synth.mixture_dense(7300 + k + nq, 19973, 256, 48, nq, k, "bf16")
@@ -105,9 +101,8 @@ def test_long_list_merge_with_a_short_last_chunk(nq, k):
 
 @pytest.mark.parametrize("nq", [100, 256])
 def test_32k_x_1024_bf16_top100(c2, nq):
-    """The hybrid's dense list shape: 32,768 x 1,024 bf16, top-100 (filtered levels 2,048 ->
-    32,768), at 100 queries (two 64-query blocks over 128-row tiles) and 256 (two 128-query
-    blocks)."""
+    """The hybrid's dense list shape: 32,768 x 1,024 bf16, top-100 of every score, at 100 and 256
+    queries."""
     log("32k bf16 top-100 nq", nq)
     q = c2.queries[:nq].contiguous()
     _, sc, ids = _run(c2.rows, q, 100, "bf16")
@@ -149,9 +144,8 @@ def test_ragged_sizes_and_k(dtype, n, nq, k):
 
 
 def _sweep_cases(n_cases=40, seed=2608):
-    """Seeded (dtype, n, d, nq, k) draws across the kernel table: dimensions whose k-step count
-    admits rings of 4, 8 or 16 (or only 4), query blocks resident or streamed, the largest
-    dimension, every batch class and both selection strategies."""
+    """Seeded (dtype, n, d, nq, k) draws: two to 128 stages a tile, the largest dimension, every tile
+    shape's batches, k on both sides of 16."""
     r = np.random.default_rng(seed)
     dims = [128, 256, 384, 640, 896, 1024, 1152, 2048, 4096, 8192]
     batches = [1, 2, 5, 16, 17, 40, 64, 65, 100, 128, 129, 200, 256, 300, 513]
@@ -168,9 +162,8 @@ def _sweep_cases(n_cases=40, seed=2608):
 
 @pytest.mark.parametrize("dtype,n,d,nq,k", _sweep_cases())
 def test_seeded_shape_sweep(dtype, n, d, nq, k):
-    """Parity over seeded shapes that reach every ring depth, resident and streamed query
-    blocks, d up to the largest supported dimension, ragged rows and batches, k on both sides
-    of the list/threshold boundary."""
+    """Parity over seeded shapes: d up to the largest supported dimension, ragged rows and batches,
+    k on both sides of 16."""
     log("sweep", dtype, n, d, nq, k)
     device()
     w = synth.mixture_dense(500 + d // 128 + nq, n, d, 24, nq, k, dtype)
@@ -182,8 +175,7 @@ def test_seeded_shape_sweep(dtype, n, d, nq, k):
 @pytest.mark.parametrize("d", [512, 1536])
 @pytest.mark.parametrize("nq", [1, 16])
 def test_small_batch_resident_and_streamed_queries(d, nq):
-    """The batch-1 to 16 top-5 kernel keeps its query block resident in LDS up to 1,024
-    dimensions: d = 512 fills four of its eight slices; d = 1,536 takes the streamed kernel."""
+    """Top-5 of 1 and 16 queries at eight and 24 stages a tile."""
     device()
     w = synth.mixture_dense(300 + d // 128, 5000, d, 16, nq, 5, "bf16")
     _, sc, ids = _run(w.rows, w.queries, 5, "bf16")
@@ -195,11 +187,10 @@ def test_small_batch_resident_and_streamed_queries(d, nq):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("nq,k", [(1, 7), (16, 5), (40, 16), (130, 5), (130, 10)])
 def test_multi_tile_chunks_exact_ties(kind, dtype, nq, k):
-    """393,293 x 128 integer rows: enough rows that every query block walks several tiles per
-    row chunk, so the selection runs against running thresholds.  "ints": entries in
+    """393,293 x 128 integer rows: every query block walks several tiles per row chunk.  "ints": entries in
     {-2..2}, exact scores with ties near the k-th value.  "four_rows": every row is one of four
-    vectors, so each tile holds dozens of rows tied at the best score and the tie handling
-    takes its overflow paths.  Ids and scores must equal the oracle's exactly."""
+    vectors, so each tile holds dozens of rows tied at the best score and the selections
+    take their paths for ties.  Ids and scores must equal the oracle's exactly."""
     device()
     g = np.random.default_rng(7000 + 31 * nq + k + (0 if kind == "ints" else 1))
     n, d = 393_216 + 77, 128
@@ -219,9 +210,8 @@ def test_multi_tile_chunks_exact_ties(kind, dtype, nq, k):
 
 @pytest.mark.parametrize("nq,k", [(1, 16), (16, 16), (3, 5), (40, 8)])
 def test_merge_with_candidates_concentrated(nq, k):
-    """32,768 rows where every fourth run of 64 rows scores high and the rest low: the best
-    entries of many per-chunk lists compete, so the list merge sees far more composites above
-    its threshold than one wave can rank at once and extracts the k best one at a time.
+    """32,768 rows where every fourth run of 64 rows scores high and the rest low, in 37 steps of
+    equal scores: many more scores reach the selection's bound than are returned.
     Integer values: ids and scores must equal the oracle's exactly."""
     device()
     n, d = 32_768, 128
@@ -243,11 +233,10 @@ def test_merge_with_candidates_concentrated(nq, k):
 @pytest.mark.parametrize("nq", [3, 70])
 @pytest.mark.parametrize("case", ["repair", "fallback"])
 def test_filtered_overflow_repair(case, nq):
-    """k > 16 runs in threshold levels with candidate buffers of max(4,096, 256 k) keys.
-    "repair": the first 4,096 rows score low, so the last level's threshold admits ~56,000
-    rows and the buffers overflow; the device-side repair reruns the last level with the
-    k-th scores found so far.  "fallback": a quarter of 120,000 rows tie at the top score,
-    so every repair overflows too and the per-chunk-list plan answers.  Exact either way."""
+    """k > 16 past 32,768 rows runs in threshold levels with candidate buffers of max(4,096, 64 k) keys.
+    "repair": the first 4,096 rows score low (levels over prefixes would overflow the buffers).
+    "fallback": a quarter of 120,000 rows tie at the top score, so the buffers overflow, the repair's as
+    well, and the group maxima of the whole index answer.  Exact either way."""
     device()
     g = np.random.default_rng(11 + nq)
     k, d = 17, 128

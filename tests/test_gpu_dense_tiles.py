@@ -81,6 +81,8 @@ def test_few_queries_with_ties_and_nan(n, nq, case):
     dev = device()
     idx = make_index(synth.to_storage(X, "bf16"), "bf16")
     sc, ids = idx.search_dense(synth.to_storage(Q, "bf16").to(dev), 16)
+    sc2, ids2 = idx.search_dense_noalloc(synth.to_storage(Q, "bf16").to(dev), 16)
+    assert torch.equal(ids, ids2) and torch.equal(sc, sc2)
     sc, ids = sc.cpu().numpy().astype(np.float64), ids.cpu().numpy()
     S = Q.astype(np.float64) @ X.astype(np.float64).T
     for i in range(nq):
@@ -102,8 +104,8 @@ def test_group_maxima_at_the_edges(dtype, d, n, nq, k):
 @pytest.mark.parametrize("n,nq,k", [(400_001, 65, 1), (400_001, 130, 10), (393_217, 300, 16), (40_007, 66, 17),
                                     (300_003, 90, 128), (200_000, 5, 100)])
 def test_threshold_levels(n, nq, k):
-    """More than 64 queries with k <= 16 past 393,216 rows, and k > 16 past 32,768: group maxima of a
-    prefix, then one or more filtered levels."""
+    """More than 64 queries with k <= 16 past 393,216 rows, and k > 16 past 32,768: group maxima of
+    some rows, then one or more filtered levels."""
     log("levels", n, nq, k)
     X, Q = _ints(n + k, n, 128, nq, spread=3)
     _check(X, Q, k, "bf16", samp=np.unique(np.r_[0:min(nq, 8), nq // 2, nq - 1]))
