@@ -523,16 +523,13 @@ constexpr long long kDumpRows = 32768;        // up to this many rows every scor
 //   d 1024: 16 x 1,000 18.6 / 13.5, 64 x 32,768 22.7 / 22.2, 256 x 10,000 21.7 / 21.4, x 32,768 31.1 / 33.9
 //   d 4096: 256 x 20,000 69.3 / 60.3; fp32 d 1024: 16 x 1,000 33.4 / 23.4
 constexpr long long kDumpScores = 1ll << 20, kDumpMost = 6ll << 20, kDumpRow = 768;
-// Batches of up to 16 over longer indexes keep every score while a chunk's fit in LDS and they add a 32nd
+// Batches of up to 16 over longer indexes keep every score while a chunk's fit in LDS and they add a 16th
 // to the index's bytes at most: reading scores back takes 4 us less than scoring rows again, and chunks
 // need not end with a tile.  bf16, k = 5, group maxima against all scores in us: 1 query over 65,536 x 1,024
 // 30.5 / 26.4, 150,000 57.0 / 53.0, 300,000 121.5 / 116.3, 1 M 353 / 347 (k = 10); 16 queries 30.7 / 27.3 and
-// 58.7 / 58.5; f16 168,344 x 512, 4 queries 37.2 / 33.9; 100,000 x 256, 4 queries 20.3 / 17.6.
-constexpr long long kScoresShare = 4 * 32;
-// k <= 16, more than 64 queries: longer indexes filter.  The line is where 512 queries gain from
-// neither; fewer queries would cross at some 800,000 rows, more at 300,000.  bf16 x 1,024, group maxima against
-// levels in us: 65 queries over 393,216 rows 167 / 195, 600,000 256 / 276, 1 M 410 / 397; 512 queries 377 / 407,
-// 565 / 585, 933 / 890; 2,048 queries over 200,000 rows 735 / 811, 393,216 1,462 / 1,345, 600,000 2,218 / 2,001.
+// 58.7 / 58.5; f16 168,344 x 512, 4 queries 37.2 / 33.9; 8 queries over 100,000 x 256 20.6 / 18.0.  More tiles than
+// LDS holds, stored in two parts: 16 queries over 300,000 x 1,024 123 / 128, 4 over 1 M 354 / 356.
+constexpr long long kScoresShare = 4 * 16;
 constexpr long long kMaximaRows = 393216;
 // Up to this many groups (one pass of the rescoring workgroup) are searched directly, which saves a
 // dependent read (1.5 us of a call; batch 1 over 32,768 rows 21.3 -> 20.0 us), unless the batch is so

@@ -53,8 +53,8 @@ def test_every_score_or_group_maxima(dtype, d, n, nq, k):
 
 
 @pytest.mark.parametrize("dtype,d,n,nq,k", [
-    # every score and the lanes' maxima: 128 bytes of a row per query, and one query more (group maxima)
-    ("bf16", 128, 32_769, 2, 16), ("bf16", 128, 33_003, 3, 5), ("f32", 100, 41_001, 3, 10), ("f32", 100, 41_001, 4, 10),
+    # every score and the lanes' maxima: 64 bytes of a row per query, and one query more (group maxima)
+    ("bf16", 128, 32_769, 4, 16), ("bf16", 128, 33_003, 5, 5), ("f32", 100, 41_001, 6, 10), ("f32", 100, 41_001, 7, 10),
     ("bf16", 1024, 32_785, 16, 16), ("f16", 256, 65_535, 4, 1),
     # tiles of a chunk times queries 80 and past it (group maxima), on 256 CUs
     ("bf16", 256, 655_360, 4, 5), ("bf16", 256, 655_361, 4, 5), ("f32", 32, 2_621_440, 1, 16),
