@@ -530,9 +530,13 @@ constexpr long long kDumpScores = 1ll << 20, kDumpMost = 6ll << 20, kDumpRow = 7
 // 58.7 / 58.5; f16 168,344 x 512, 4 queries 37.2 / 33.9; 8 queries over 100,000 x 256 20.6 / 18.0.  More tiles than
 // LDS holds, stored in two parts: 16 queries over 300,000 x 1,024 123 / 128, 4 over 1 M 354 / 356.
 constexpr long long kScoresShare = 4 * 16;
+// k <= 16, more than 64 queries: longer indexes filter.  The line is where 512 queries gain from neither;
+// fewer queries would cross at some 800,000 rows, more at 300,000.  bf16 x 1,024, group maxima against
+// levels in us: 65 queries over 393,216 rows 167 / 195, 600,000 256 / 276, 1 M 410 / 397; 512 queries 377 / 407,
+// 565 / 585, 933 / 890; 2,048 queries over 200,000 rows 735 / 811, 393,216 1,462 / 1,345, 600,000 2,218 / 2,001.
 constexpr long long kMaximaRows = 393216;
 // Up to this many groups (one pass of the rescoring workgroup) are searched directly, which saves a
-// dependent read (1.5 us of a call; batch 1 over 32,768 rows 21.3 -> 20.0 us), unless the batch is so
+// dependent read (1.5 us of a call; batch 1 over 32,768 rows, by group maxima, 21.3 -> 20.0 us), unless the batch is so
 // large that the maxima's bytes count (batch 1,024: 15.6 us, 14.5 through the coarse ones).
 constexpr int kOneLevel = 8192;
 constexpr long long kFilterMin = 4096;        // fewest rows of the first level
@@ -540,9 +544,9 @@ constexpr long long kFilterFirst = 32000;     // most rows of the first level
 // Row growth between levels.  A level's hits cost its tiles time in proportion (at 16-fold growth and k
 // = 100, a hit in 5,000 scores, a fifth of it), a level itself two launches.
 constexpr long long filter_grow(int k) { return k <= 16 ? 8 : 4; }
-// Filter, k <= 16: candidate slots per query.  A query whose best rows no level but the first and the last
-// has (a topic between two tiles) collects about 64 k, 1,024 at k = 16, and half as many again one time in a
-// few thousand at 2,048 slots.
+// Filter, k <= 16: candidate slots per query.  A query whose best rows only the first and the last level have
+// (a topic that lies between two tiles of the others) collects about 64 k, 1,024 at k = 16, but the sample of
+// k rows varies: of 300 such queries 2 overflowed 2,048 slots.
 constexpr long long kSmallCap = 3072;
 
 size_t align_up256(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -730,8 +730,8 @@ __global__ __launch_bounds__(kTileThreads) void dense_tile_kernel(DenseArgs a) {
 // the bound are read back, four rows a word, and the scores that reach it are ranked: 4 us less than with rows
 // scored again.
 //
-// A launch of a few workgroups is bound by latency.  One query over 32,768 rows of 1,024 bf16 takes
-// 7.0 us from start to end: 1.4 the maxima (the first reads), 0.7 tau, 1.1 the groups' order, 2.6 the
+// A launch of a few workgroups is bound by latency.  One query over 32,768 rows of 1,024 bf16 (a size that has
+// come to select from every score instead) takes 7.0 us from start to end: 1.4 the maxima (the first reads), 0.7 tau, 1.1 the groups' order, 2.6 the
 // rows, 0.8 their ranks.  It took 10.7 unrolled over the keys (28 KB of code fetched cold), so the code
 // is kept short: the maxima are held as one per 16-byte word, and a word that holds a hit is read
 // again; and 8.0 with tau counted by v_readlane and a test before each step's matrix instruction.
