@@ -89,3 +89,32 @@ def test_fp32_levels(n, nq, k):
     sc, ids = idx.search_dense(Q, k)
     _check(X, Q, k, sc, ids, [0, nq // 2, nq - 1])
     idx.close()
+
+
+@pytest.mark.parametrize("dtype,d,n,nq,k", [("bf16", 128, 5_000, 4, 5),       # every score
+                                            ("bf16", 128, 50_003, 2, 10),     # every score and the lanes' maxima
+                                            ("f32", 8, 300_000, 33, 10),      # group maxima
+                                            ("bf16", 128, 400_100, 70, 10),   # levels
+                                            ("f16", 128, 40_001, 3, 40)])
+def test_captured_search_replays_on_new_queries(dtype, d, n, nq, k):
+    """One capture, several replays on other queries with eager searches between them."""
+    log("capture", dtype, d, n, nq, k)
+    idx, X, Q = _index(n + k, n, d, nq, dtype, 7)
+    q = Q.clone()
+    out = (torch.empty((nq, k), device=q.device), torch.empty((nq, k), dtype=torch.int64, device=q.device))
+    idx.search_dense(q, k, out=out)  # the workspace exists before the capture
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        idx.search_dense(q, k, out=out)
+    for r in range(4):
+        q.copy_(Q.roll(r, 0) * (1 if r % 2 else -1))
+        out[0].fill_(7.0)
+        out[1].fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        sc, ids = out[0].clone(), out[1].clone()
+        esc, eids = idx.search_dense(q, k)
+        assert torch.equal(ids, eids) and torch.equal(sc, esc)
+        _check(X, q, k, sc, ids, [0, nq - 1])
+    idx.close()
